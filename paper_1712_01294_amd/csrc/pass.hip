@@ -214,13 +214,11 @@ __device__ bool newton_h(const double* __restrict__ rl, long long n, int i, int 
     return false;
 }
 
-// Group scans per particle: particles the first round does not finish (no
-// bracket yet, or more radii than the list holds) go to the per-particle solver,
-// which is cheaper for them than further group passes over a sparse class.
-constexpr int kScanRounds = 1;
-constexpr double kColdPad = 1.05;   // first scan radius over a cold guess
-constexpr double kWarmPad = 1.03;   // first scan radius over the previous H
-constexpr double kStoreCold = 1.05;   // radii listed by a cold first scan, over the guess
+// Each particle takes one group scan; those it does not finish (no bracket, or
+// more radii than the list holds) go to the per-particle solver, which is
+// cheaper for them than further group passes over a sparse class.
+constexpr double kColdPad = 1.05;   // scan radius over a cold guess
+constexpr double kWarmPad = 1.03;   // scan radius over the previous H
 // a scan pass takes the lanes with R >= kClassRatio Rref within kClassWindow Rref
 // of the first of them on every axis (Rref: the largest trial radius pending).
 // Fewer, wider classes pay down to a quarter: each pass scans the union once,
@@ -228,13 +226,13 @@ constexpr double kStoreCold = 1.05;   // radii listed by a cold first scan, over
 constexpr double kClassRatio = 0.25;
 constexpr double kClassWindow = 2.0;
 
-// Five waves per SIMD (96 VGPRs): the scan is latency-bound, and the extra wave
-// outweighs the few loop-invariant values this budget spills to scratch.
+// Four waves per SIMD: 128 VGPRs, and the 37 KB of staged candidates per block
+// fit four times in the LDS of a compute unit.
 // With HIER (hierarchical steps with active subsets) only the particles of
 // mode 1 solve; the others keep their kernel length.  The cell tables may then
 // be those of an earlier build: every scan reaches *pad further, the largest
 // distance a particle has moved since.
-constexpr int kSolveWaves = 5;
+constexpr int kSolveWaves = 4;
 template <bool HIER>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves))) void k_solve_h(PassArrays a, TreeDesc td, const int2* __restrict__ tab,
                                                   const double4* __restrict__ pos, Phys ph, Counters* cnt,
@@ -243,8 +241,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
                                                   int* __restrict__ fb_list, unsigned long long* __restrict__ fb_count,
                                                   const unsigned char* __restrict__ mode, const double* __restrict__ pad) {
     cnt = counter_copy(cnt);
-    __shared__ ScanLds lds[256 / kWave];
-    ScanLds& S = lds[threadIdx.x / kWave];
+    __shared__ GroupLds lds[256 / kWave];
+    GroupLds& S = lds[threadIdx.x / kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int i = xcd_block() * 256 + threadIdx.x;
     const bool act = i < a.n && (!HIER || mode[i] == kModeSolve);
@@ -255,7 +253,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
     for (int d = 0; d < 3; d++)
         if (ph.periodic[d]) half = fmin(half, 0.5 * ph.box[d]);
     double xi[3] = {0.0, 0.0, 0.0};
-    double guess = 0.0;
+    double R = 0.0, guess = 0.0;   // scan radius
     bool warm = false;
     if (act) {
         const double4 pi = pos[i];
@@ -265,29 +263,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
         guess = a.H[i];
         warm = guess > 0.0;
         if (!warm) guess = cold_guess(td, tab, xi, ph.n_ngb, a.n);
+        R = (warm ? kWarmPad : kColdPad) * guess;
+        if (R >= half) R = half * (1.0 - 1e-12);
     }
-    // state 0: scanning, 1: bracketed with every radius below hi listed, 2: given up
-    int state = act ? 0 : 2;
-    double lo = 0.0, hi = INFINITY, top = INFINITY;   // top: smallest R whose list overflowed
-    double R = (warm ? kWarmPad : kColdPad) * guess;
-    double neff_hi = 0.0, fa = NAN;                   // residuals at the bracket ends
-    int m = 0, rounds = 0;
-    unsigned long long iters = 0;
-    for (int pass = 0; pass < kScanRounds * kWave; pass++) {
-        if (state == 0 && (rounds >= kScanRounds || !(R > lo))) state = 2;
-        if (state == 0 && !(R < half)) {
-            R = half * (1.0 - 1e-12);
-            if (!(R > lo)) state = 2;   // the root lies beyond half a periodic side
-        }
-        const bool need = state == 0;
+    // Weighted counts at R and at two trial lengths: below the guess (at it on a
+    // cold start) and at the scan radius again, formed from the guess; the radii
+    // below Sl are listed.
+    const double Hg = R * (warm ? 1.0 / kWarmPad : 1.0 / kColdPad);
+    const double Ht0 = warm ? 0.97 * Hg : Hg, Ht1 = (warm ? kWarmPad : kColdPad) * Hg;
+    const double Sl = warm ? R : Ht1;
+    double sw = 0.0, st0 = 0.0, st1 = 0.0;
+    int m = 0;   // radii met, listed while they fit
+    bool need = act && R > 0.0;
+    for (int pass = 0; pass < kWave; pass++) {
         if (__ballot(need) == 0) break;
-        // this pass: lanes within 2x of the largest radius and within 2 Rref of the first such lane
+        // this pass: lanes within kClassRatio of the largest radius and close to the first such lane
         const double Rref = uniform_d(wave_max_d(need ? R : 0.0));
         const bool big = need && R >= kClassRatio * Rref;
         const int leader = __builtin_amdgcn_readfirstlane(__ffsll((long long)__ballot(big)) - 1);
+        const double win = kClassWindow * Rref;
         const double xl0 = uniform_d(__shfl(xi[0], leader, kWave)), xl1 = uniform_d(__shfl(xi[1], leader, kWave)),
                      xl2 = uniform_d(__shfl(xi[2], leader, kWave));
-        const double win = kClassWindow * Rref;
         const bool cls = big && fabs(xi[0] - xl0) <= win && fabs(xi[1] - xl1) <= win && fabs(xi[2] - xl2) <= win;
         const double Rq = uniform_d(wave_max_d(cls ? R : 0.0));
         double bmin[3], bmax[3];
@@ -295,24 +291,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
             bmin[d] = uniform_d(wave_min_d(cls ? xi[d] : INFINITY));
             bmax[d] = uniform_d(wave_max_d(cls ? xi[d] : -INFINITY));
         }
-        const double R2 = R * R;
-        // Weighted counts at R and at two trial lengths.  The first scan of a
-        // cold start lists only the radii below kStoreCold times the guess (a
-        // scan radius padded further brackets more roots in one scan; with the
-        // default pads, equal to kStoreCold, every radius within R is listed),
-        // with the trial lengths at the guess and at that limit; if the root lies
-        // above the limit, the bracket is kept and one more scan lists them all.
-        const bool part = !warm && rounds == 0 && kStoreCold > 0.0;
-        const double Hg = R * (warm ? 1.0 / kWarmPad : 1.0 / kColdPad);
-        const double Ht[2] = {part ? Hg : 0.97 * Hg, part ? kStoreCold * Hg : 1.03 * Hg};
-        const double Sl = part ? Ht[1] : R;   // radii below Sl are listed
-        const double iR = 1.0 / R, iT0 = 1.0 / Ht[0], iT1 = 1.0 / Ht[1];
-        double sw = 0.0, st0 = 0.0, st1 = 0.0;
-        if (cls) {
-            rounds++;
-            m = 0;
-        }
-        group_scan(td, tab, pos, S, lane, bmin, bmax, HIER ? Rq + *pad : Rq, xi, R2, cls, [&](int j, double r2) {
+        const double iR = 1.0 / R, iT0 = 1.0 / Ht0, iT1 = 1.0 / Ht1;
+        group_scan(td, tab, pos, S, lane, bmin, bmax, Rq, HIER ? *pad : 0.0, xi, R * R, cls, [&](int j, double r2) {
             const double r = sqrt(r2);
             if (r < Sl) {
                 if (m < cap) {
@@ -325,61 +305,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
             st0 += spline_w(r * iT0);
             st1 += spline_w(r * iT1);
         });
-        if (cls) {
-            const double neff = c32 * sw;
-            if (neff < ph.n_ngb) {
-                lo = R;
-                if (hi < INFINITY) {
-                    R = 0.5 * (lo + hi);
-                } else {
-                    // grow by the density estimate, at least 1.15x, at most 4x,
-                    // and not past a radius known to overflow
-                    const double g = 1.1 * cbrt(ph.n_ngb / fmax(neff, 1e-300));
-                    R *= fmin(4.0, fmax(1.15, g));
-                    if (top < INFINITY) R = fmin(R, 0.5 * (lo + top));
-                }
-            } else if (m > cap) {
-                // bracketed, but too many radii to keep: rescan just above the estimated root
-                hi = R;
-                top = fmin(top, R);
-                R = fmax(lo + 0.25 * (hi - lo), fmin(1.05 * R * cbrt(ph.n_ngb / neff), R * cbrt(0.8 * cap / m)));
-                if (!(R < hi)) R = 0.5 * (lo + hi);
-            } else {
-                // every radius below R is listed: narrow the bracket with the trial counts
-                // (summed in the same order as the Newton sums, so the signs agree)
-                hi = R;
-                neff_hi = neff;
-                const double f0 = c32 * st0 - ph.n_ngb, f1 = c32 * st1 - ph.n_ngb;
-                fa = NAN;
-                if (Ht[1] < hi && Ht[1] > lo) {
-                    if (f1 >= 0.0) hi = Ht[1], neff_hi = f1 + ph.n_ngb;
-                    else lo = Ht[1], fa = f1;
-                }
-                if (Ht[0] < hi && Ht[0] > lo) {
-                    if (f0 >= 0.0) hi = Ht[0], neff_hi = f0 + ph.n_ngb;
-                    else lo = Ht[0], fa = f0;
-                }
-                if (hi > Sl) {
-                    // the root lies above the listed radii: list them all up to hi
-                    R = hi;
-                } else {
-                    state = 1;
-                }
-            }
+        need = need && !cls;
+    }
+    // A bracket with every radius below it listed is narrowed by the trial counts
+    // (summed in the order of the Newton sums, so the signs agree).  Newton starts
+    // from the secant of the bracket when both ends carry a residual, else from
+    // the density scaling of the upper end.
+    const double neff = c32 * sw;
+    double lo = 0.0, hi = R, neff_hi = neff, fa = NAN;
+    bool found = act && neff >= ph.n_ngb && m <= cap;
+    if (found) {
+        const double f0 = c32 * st0 - ph.n_ngb, f1 = c32 * st1 - ph.n_ngb;
+        if (Ht1 < hi) {
+            if (f1 >= 0.0) hi = Ht1, neff_hi = f1 + ph.n_ngb;
+            else lo = Ht1, fa = f1;
         }
+        if (Ht0 < hi && Ht0 > lo) {
+            if (f0 >= 0.0) hi = Ht0, neff_hi = f0 + ph.n_ngb;
+            else lo = Ht0, fa = f0;
+        }
+        found = !(hi > Sl);   // else the root lies above the listed radii
     }
     bool conv = false;
     double Hc = 0.0;
-    if (state == 1) {
-        // start from the secant of the bracket when both ends carry a residual,
-        // else from the density scaling of the upper end
+    unsigned long long iters = 0;
+    if (found) {
         const double fb = neff_hi - ph.n_ngb;
         if (fa < 0.0 && fb >= 0.0) Hc = lo + (hi - lo) * (-fa / (fb - fa));
         else Hc = (warm && guess > lo && guess < hi) ? guess : hi * cbrt(ph.n_ngb / neff_hi);
         if (!(Hc > lo && Hc <= hi)) Hc = 0.5 * (lo + hi);
         conv = newton_h(rl, n, i, m, ph.n_ngb, ph.h_maxit, lo, hi, Hc, iters);
     }
-    if (state == 1 && conv) {
+    if (conv) {
         double sum = 0.0;
         const double iH = 1.0 / Hc;
         int c = 0;
@@ -402,18 +359,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
     } else if (act) {
         // hand over to the per-particle solver: the bracket and the next trial
         // radius, in the particle's own (now unused) radius slots 0-2
+        double Rn = R;
+        if (!(R > 0.0)) {
+            // no scan without a radius (positions that are not numbers)
+            hi = INFINITY;
+        } else if (!(neff >= ph.n_ngb)) {
+            // grow by the density estimate, at least 1.15x, at most 4x
+            lo = R;
+            hi = INFINITY;
+            Rn = R * fmin(4.0, fmax(1.15, 1.1 * cbrt(ph.n_ngb / fmax(neff, 1e-300))));
+        } else if (m > cap) {
+            // bracketed, but too many radii to keep: just above the estimated root
+            Rn = fmax(lo + 0.25 * (hi - lo), fmin(1.05 * R * cbrt(ph.n_ngb / neff), R * cbrt(0.8 * cap / m)));
+            if (!(Rn < hi)) Rn = 0.5 * (lo + hi);
+        } else if (hi > Sl) {
+            Rn = hi;
+        }
         const unsigned long long slot = atomicAdd(fb_count, 1ull);
         if (slot < (unsigned long long)a.n) fb_list[slot] = i;
         rl[i] = lo;
         rl[n + i] = hi;
-        rl[2 * n + i] = R;
-        a.H[i] = (hi < INFINITY) ? hi : (lo > 0.0 ? lo : guess);
+        rl[2 * n + i] = Rn;
+        a.H[i] = hi < INFINITY ? hi : (lo > 0.0 ? lo : guess);
     }
-    const unsigned long long rr = (unsigned long long)rounds;
-    count_add(&cnt->h_iters, iters + rr);
-    count_max(&cnt->h_iters_max, iters + rr);
-    count_max(&cnt->h_rounds_max, rr);
-    count_add(&cnt->h_rounds3, rounds >= 3 ? 1ull : 0ull);
+    const unsigned long long its = iters + (act ? 1ull : 0ull);
+    count_add(&cnt->h_iters, its);
+    count_max(&cnt->h_iters_max, its);
+    count_max(&cnt->h_rounds_max, act ? 1ull : 0ull);
 }
 
 // Particles the group scan hands over, one wave each.  The wave scans the cells
@@ -741,8 +713,8 @@ __global__ __launch_bounds__(256) void k_gather_kept(PassArrays a, TreeDesc td, 
                                                      const unsigned char* __restrict__ mode, const double* __restrict__ pad,
                                                      int* __restrict__ jl, int* __restrict__ gcount,
                                                      int* __restrict__ counts) {
-    __shared__ ScanLds lds[256 / kWave];
-    ScanLds& S = lds[threadIdx.x / kWave];
+    __shared__ GroupLds lds[256 / kWave];
+    GroupLds& S = lds[threadIdx.x / kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int i = xcd_block() * 256 + threadIdx.x;
     const bool sel = i < a.n && mode[i] == kModeKept;
@@ -767,7 +739,7 @@ __global__ __launch_bounds__(256) void k_gather_kept(PassArrays a, TreeDesc td, 
     }
     const int cap = ph.max_ngb;
     int c = 0;
-    group_scan(td, tab, pos, S, lane, bmin, bmax, Rq + *pad, xi, Rs * Rs, sel, [&](int j, double r2) {
+    group_scan(td, tab, pos, S, lane, bmin, bmax, Rq, *pad, xi, Rs * Rs, sel, [&](int j, double r2) {
         const double r = sqrt(r2);
         if (r < H && j != i) {
             if (c < cap) jl[(long long)c * n + i] = j;

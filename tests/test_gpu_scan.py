@@ -1,0 +1,77 @@
+"""The neighbour search of the kernel-length solve against brute force: every
+flux list equals the set r < max(H_i, H_j) as integers, and every H solves
+(32/3) sum_j w(r_ij / H) = n_ngb over all particles, on sets whose groups span
+wide ranges of radii, distances and cell sizes."""
+import numpy as np
+import pytest
+
+from paper_1712_01294_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+# a sum of at most a few hundred kernel weights <= 1, each rounded to 2^-53 of
+# its value and the sum to n_ngb, relative to n_ngb: below 1e-13
+TOL_COUNT = 1e-12
+
+
+def _set(kind, n, seed):
+    rng = np.random.default_rng(seed)
+    box, per = (1.0, 1.0, 1.0), (1, 1, 1)
+    if kind == "uniform":
+        X = rng.uniform(0, 1, (3, n))
+    elif kind == "slab":
+        box = (4.0, 1.0, 0.25)
+        X = rng.uniform(0, 1, (3, n)) * np.array(box)[:, None]
+    else:
+        # two tight clumps in a wide open box: finest cells hold thousands of
+        # particles and lie far beyond the spheres of the clumps' members
+        box, per = (1000.0, 1000.0, 1000.0), (0, 0, 0)
+        X = rng.uniform(0, 1000, (3, n))
+        k = n // 4
+        X[:, :k] = 300.0 + 0.5 * rng.normal(size=(3, k))
+        X[:, k:2 * k] = 302.0 + 0.02 * rng.normal(size=(3, k))
+    return W.Workload(name=kind, x=X[0].copy(), y=X[1].copy(), z=X[2].copy(), m=np.full(n, 1.0 / n),
+                      vx=rng.normal(0, 0.1, n), vy=rng.normal(0, 0.1, n), vz=rng.normal(0, 0.1, n),
+                      u=np.full(n, 1.5), gamma=5.0 / 3.0, box=box, periodic=per)
+
+
+@pytest.mark.parametrize("kind,n", [("uniform", 300), ("uniform", 70001), ("slab", 66000), ("clumps", 2500),
+                                    ("clumps", 70003)])
+def test_lists_and_kernel_lengths_equal_brute_force(kind, n):
+    import torch
+
+    from paper_1712_01294_amd import mfm
+    w = _set(kind, n, W.SEED_BASE + 700 + n)
+    ctx = mfm.Context(mfm.config_of(w, max_ngb=16384), n)
+    st = mfm.State.from_arrays(w.arrays())
+    ctx.build_neighbours(st)
+    ctx.hydro_pass(st)
+    ctx.check(allow_illcond=True)
+    counts, lst = ctx.flux_lists(n)
+    X, H = torch.stack([st.x, st.y, st.z]), st.H
+    box = torch.tensor(w.box, dtype=torch.float64, device="cuda")
+    worst = 0.0
+    step = max(1, 40_000_000 // n)
+    for a in range(0, n, step):
+        b = min(n, a + step)
+        r2 = torch.zeros(b - a, n, dtype=torch.float64, device="cuda")
+        for c in range(3):
+            d = X[c][None, :] - X[c][a:b, None]
+            if w.periodic[c]:
+                d -= box[c] * torch.round(d / box[c])
+            r2 += d * d
+        r = torch.sqrt(r2)
+        q = r / H[a:b, None]
+        t, h = (1 - q).clamp(min=0), (0.5 - q).clamp(min=0)
+        s = (32.0 / 3.0) * (2 * t ** 3 - 8 * h ** 3).sum(1)
+        worst = max(worst, float((s / w.n_ngb - 1).abs().max()))
+        want = r < torch.maximum(H[a:b, None], H[None, :])
+        want[torch.arange(b - a, device="cuda"), torch.arange(a, b, device="cuda")] = False
+        got = torch.zeros_like(want)
+        k = torch.arange(lst.shape[0], device="cuda")[:, None]
+        used = k < counts[a:b][None, :]
+        got[torch.arange(b - a, device="cuda").expand_as(used)[used], lst[:, a:b][used].long()] = True
+        assert torch.equal(counts[a:b].long(), want.sum(1)), (kind, a)
+        assert torch.equal(got, want), (kind, a)
+    print(f"{kind} {n}: residual of the neighbour-number equation {worst:.2e}", flush=True)
+    assert worst <= TOL_COUNT
