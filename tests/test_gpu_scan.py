@@ -27,7 +27,7 @@ def _set(kind, n, seed):
         # particles and lie far beyond the spheres of the clumps' members
         box, per = (1000.0, 1000.0, 1000.0), (0, 0, 0)
         X = rng.uniform(0, 1000, (3, n))
-        k = n // 4
+        k = min(n // 4, 1500)
         X[:, :k] = 300.0 + 0.5 * rng.normal(size=(3, k))
         X[:, k:2 * k] = 302.0 + 0.02 * rng.normal(size=(3, k))
     return W.Workload(name=kind, x=X[0].copy(), y=X[1].copy(), z=X[2].copy(), m=np.full(n, 1.0 / n),
@@ -42,7 +42,7 @@ def test_lists_and_kernel_lengths_equal_brute_force(kind, n):
 
     from paper_1712_01294_amd import mfm
     w = _set(kind, n, W.SEED_BASE + 700 + n)
-    ctx = mfm.Context(mfm.config_of(w, max_ngb=16384), n)
+    ctx = mfm.Context(mfm.config_of(w, max_ngb=4096), n)
     st = mfm.State.from_arrays(w.arrays())
     ctx.build_neighbours(st)
     ctx.hydro_pass(st)
