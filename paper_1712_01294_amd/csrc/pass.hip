@@ -37,6 +37,17 @@ __device__ __forceinline__ unsigned long long wave_max(unsigned long long v) {
     return v;
 }
 
+__device__ __forceinline__ int wave_min_i(int v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
+    return v;
+}
+__device__ __forceinline__ int wave_max_i(int v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
+    return v;
+}
+
 __device__ __forceinline__ void count_add(unsigned long long* c, unsigned long long v) {
     v = wave_sum(v);
     if ((threadIdx.x & 63) == 0 && v) atomicAdd(c, v);
@@ -171,6 +182,20 @@ __device__ double cold_guess(const TreeDesc& td, const int2* __restrict__ tab, c
     return cbrt(3.0 * n_ngb * vol / (4.0 * M_PI * count));
 }
 
+// products and sums rounded one by one (contraction into fma is switched off
+// here), so that an expression gives the same bits wherever it is compiled: the
+// face sum whichever owner evaluates it, a residual whichever kernel forms it
+template <typename T>
+__device__ __forceinline__ T mul_rn(T x, T y) {
+#pragma clang fp contract(off)
+    return x * y;
+}
+template <typename T>
+__device__ __forceinline__ T add_rn(T x, T y) {
+#pragma clang fp contract(off)
+    return x + y;
+}
+
 constexpr double kNewtonTail = 1e-9;   // last Newton step accepted without a check pass
 
 // One safeguarded Newton update from the residual f and slope fp at Hc, inside
@@ -193,25 +218,6 @@ __device__ __forceinline__ bool newton_step(double f, double fp, double& lo, dou
     const double dH = fabs(Hn - Hc);
     Hc = Hn;
     return dH <= 1e-14 * Hc || !(hi - lo > 4e-16 * hi);
-}
-
-// safeguarded Newton on the m radii rl[k * n + i]; returns converged
-__device__ bool newton_h(const double* __restrict__ rl, long long n, int i, int m, double n_ngb, int maxit,
-                         double& lo, double& hi, double& Hc, unsigned long long& iters) {
-    const double c32 = 32.0 / 3.0;
-    for (int it = 0; it < maxit; it++) {
-        iters++;
-        const double iH = 1.0 / Hc;
-        double s = 0.0, sq = 0.0;
-#pragma unroll 8
-        for (int k = 0; k < m; k++) {
-            const double q = rl[(long long)k * n + i] * iH;
-            s += spline_w(q);
-            sq += spline_qdw(q);
-        }
-        if (newton_step(c32 * s - n_ngb, -c32 * sq * iH, lo, hi, Hc)) return true;
-    }
-    return false;
 }
 
 // Each particle takes one group scan; those it does not finish (no bracket, or
@@ -315,7 +321,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
     double lo = 0.0, hi = R, neff_hi = neff, fa = NAN;
     bool found = act && neff >= ph.n_ngb && m <= cap;
     if (found) {
-        const double f0 = c32 * st0 - ph.n_ngb, f1 = c32 * st1 - ph.n_ngb;
+        const double f0 = add_rn(mul_rn(c32, st0), -ph.n_ngb), f1 = add_rn(mul_rn(c32, st1), -ph.n_ngb);
         if (Ht1 < hi) {
             if (f1 >= 0.0) hi = Ht1, neff_hi = f1 + ph.n_ngb;
             else lo = Ht1, fa = f1;
@@ -326,36 +332,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
         }
         found = !(hi > Sl);   // else the root lies above the listed radii
     }
-    bool conv = false;
-    double Hc = 0.0;
-    unsigned long long iters = 0;
     if (found) {
+        // Newton's start and bracket, for the root kernel
         const double fb = neff_hi - ph.n_ngb;
+        double Hc;
         if (fa < 0.0 && fb >= 0.0) Hc = lo + (hi - lo) * (-fa / (fb - fa));
         else Hc = (warm && guess > lo && guess < hi) ? guess : hi * cbrt(ph.n_ngb / neff_hi);
         if (!(Hc > lo && Hc <= hi)) Hc = 0.5 * (lo + hi);
-        conv = newton_h(rl, n, i, m, ph.n_ngb, ph.h_maxit, lo, hi, Hc, iters);
-    }
-    if (conv) {
-        double sum = 0.0;
-        const double iH = 1.0 / Hc;
-        int c = 0;
-#pragma unroll 4
-        for (int k = 0; k < m; k++) {
-            const double r = rl[(long long)k * n + i];
-            sum += spline_w(r * iH);
-            const int j = jl[(long long)k * n + i];
-            if (r < Hc && j != i) {
-                jl[(long long)c * n + i] = j;
-                c++;
-            }
-        }
-        const double nk = kernel_norm(Hc) * sum;
         a.H[i] = Hc;
-        a.nk[i] = nk;
-        a.V[i] = 1.0 / nk;
-        gcount[i] = c;
-        counts[i] = c;
+        a.nk[i] = lo;
+        a.V[i] = hi;
+        gcount[i] = m;
     } else if (act) {
         // hand over to the per-particle solver: the bracket and the next trial
         // radius, in the particle's own (now unused) radius slots 0-2
@@ -381,12 +368,130 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
         rl[n + i] = hi;
         rl[2 * n + i] = Rn;
         a.H[i] = hi < INFINITY ? hi : (lo > 0.0 ? lo : guess);
+        gcount[i] = 0;   // nothing for the root kernel
     }
-    const unsigned long long its = iters + (act ? 1ull : 0ull);
-    count_add(&cnt->h_iters, its);
-    count_max(&cnt->h_iters_max, its);
+    count_add(&cnt->h_iters, act ? 1ull : 0ull);
+    count_max(&cnt->h_iters_max, act ? 1ull : 0ull);
     count_max(&cnt->h_rounds_max, act ? 1ull : 0ull);
 }
+
+// The root of each particle the group scan bracketed, one thread per particle:
+// safeguarded Newton on its listed radii from the start in H and the bracket
+// in nk and V, then nk, V and the gather list.  The first kRootRadii radii sit
+// in registers (every index fixed at compile time, a wave runs as far as its
+// longest list; slots past a lane's own hold a radius beyond the bracket, whose
+// terms are zero), so the list is read once: read again by every iteration at
+// the scan kernel's four waves per SIMD, this part waited on the lists for
+// 0.53 of the scan's 1.34 ms (lattice, 2.1M) and 11 of 29 ms (clustered, 16.8M).
+// Three waves per SIMD hold 64 radii each, which covers most waves' lists.
+// Measured (solve stage): lattice 2.1M 1.41 -> 1.29 ms, clustered 16.8M
+// 36.8 -> 31.7 ms.
+constexpr int kRootRadii = 64;
+constexpr int kRootBlock = 8;
+constexpr int kRootWaves = 3;
+template <bool HIER>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kRootWaves))) void k_root_h(
+    PassArrays a, double n_ngb, int maxit, Counters* cnt, double* __restrict__ rl, int* __restrict__ jl,
+    int* __restrict__ gcount, int* __restrict__ counts, int* __restrict__ fb_list,
+    unsigned long long* __restrict__ fb_count, const unsigned char* __restrict__ mode) {
+    cnt = counter_copy(cnt);
+    const int i = xcd_block() * 256 + threadIdx.x;
+    const long long n = a.n;
+    const double c32 = 32.0 / 3.0;
+    int m = 0;
+    double Hc = 1.0, lo = 0.0, hi = 1.0;
+    if (i < a.n && (!HIER || mode[i] == kModeSolve)) m = gcount[i];
+    if (m > 0) {
+        Hc = a.H[i];
+        lo = a.nk[i];
+        hi = a.V[i];
+    }
+    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i(min(m, kRootRadii)));
+    double r[kRootRadii];
+#pragma unroll
+    for (int b = 0; b < kRootRadii; b += kRootBlock)
+        if (b < kmax) {
+#pragma unroll
+            for (int k = b; k < b + kRootBlock; k++) r[k] = k < m ? rl[k * n + i] : 2.0 * hi;
+        }
+    unsigned long long iters = 0;
+    bool conv = false;
+    if (m > 0) {
+        for (int it = 0; it < maxit; it++) {
+            iters++;
+            const double iH = 1.0 / Hc;
+            double s = 0.0, sq = 0.0;
+#pragma unroll
+            for (int b = 0; b < kRootRadii; b += kRootBlock)
+                if (b < kmax) {
+#pragma unroll
+                    for (int k = b; k < b + kRootBlock; k++) {
+                        const double q = r[k] * iH;
+                        s += spline_w(q);
+                        sq += spline_qdw(q);
+                    }
+                }
+#pragma unroll 4
+            for (int k = kRootRadii; k < m; k++) {
+                const double q = rl[k * n + i] * iH;
+                s += spline_w(q);
+                sq += spline_qdw(q);
+            }
+            if (newton_step(add_rn(mul_rn(c32, s), -n_ngb), -c32 * sq * iH, lo, hi, Hc)) {
+                conv = true;
+                break;
+            }
+        }
+    }
+    if (conv) {
+        // the indices with r < H but the particle itself, compacted in place (a
+        // block's indices are read before any slot of the block is written)
+        double sum = 0.0;
+        const double iH = 1.0 / Hc;
+        int c = 0;
+#pragma unroll
+        for (int b = 0; b < kRootRadii; b += kRootBlock)
+            if (b < kmax) {
+                int j[kRootBlock];
+#pragma unroll
+                for (int k = 0; k < kRootBlock; k++) j[k] = b + k < m ? jl[(b + k) * n + i] : i;
+#pragma unroll
+                for (int k = 0; k < kRootBlock; k++) {
+                    sum += spline_w(r[b + k] * iH);
+                    if (r[b + k] < Hc && j[k] != i) {
+                        jl[c * n + i] = j[k];
+                        c++;
+                    }
+                }
+            }
+        for (int k = kRootRadii; k < m; k++) {
+            const double rk = rl[k * n + i];
+            sum += spline_w(rk * iH);
+            const int j = jl[k * n + i];
+            if (rk < Hc && j != i) {
+                jl[c * n + i] = j;
+                c++;
+            }
+        }
+        const double nk = kernel_norm(Hc) * sum;
+        a.H[i] = Hc;
+        a.nk[i] = nk;
+        a.V[i] = 1.0 / nk;
+        gcount[i] = c;
+        counts[i] = c;
+    } else if (m > 0) {
+        // not converged: the bracket goes on to the per-particle solver
+        const unsigned long long slot = atomicAdd(fb_count, 1ull);
+        if (slot < (unsigned long long)a.n) fb_list[slot] = i;
+        rl[i] = lo;
+        rl[n + i] = hi;
+        rl[2 * n + i] = hi;
+        a.H[i] = hi;
+    }
+    count_add(&cnt->h_iters, iters);
+    count_max(&cnt->h_iters_max, iters + 1);
+}
+
 
 // Particles the group scan hands over, one wave each.  The wave scans the cells
 // within a trial radius once and keeps every radius and index within it in
@@ -778,17 +883,6 @@ __device__ __forceinline__ void bitonic_net(int* v) {
                     v[l] = up ? hi_v : lo_v;
                 }
             }
-}
-
-__device__ __forceinline__ int wave_min_i(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ __forceinline__ int wave_max_i(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
-    return v;
 }
 
 // The tail of particle i (entries gcount[i] .. counts[i]-1 of its flux list,
@@ -1236,20 +1330,6 @@ template <>
 __device__ __forceinline__ double tsqrt<double>(double v) { return sqrt(v); }
 template <>
 __device__ __forceinline__ float tsqrt<float>(float v) { return sqrtf(v); }
-
-// One unordered pair, left state a (lower index), right state b, d = x_b - x_a.
-// products and sums rounded one by one (contraction into fma is switched off
-// here): the face sum is then the same bits whichever owner evaluates it
-template <typename T>
-__device__ __forceinline__ T mul_rn(T x, T y) {
-#pragma clang fp contract(off)
-    return x * y;
-}
-template <typename T>
-__device__ __forceinline__ T add_rn(T x, T y) {
-#pragma clang fp contract(off)
-    return x + y;
-}
 
 // One unordered pair in canonical order (the lower index is the left state),
 // evaluated by the owner `m` of one side with the record `o` of the other; mL
@@ -1706,6 +1786,8 @@ void launch_solve_h(const PassArrays& a, const TreeDesc& td, const int2* tab,
     if (t0) hipEventRecord(t0, s);
     k_solve_h<false><<<blocks_of(a.n, 256), 256, 0, s>>>(a, td, tab, pos, ph, cnt, rl, list, gcount, counts,
                                                          fb_list, fb_count, nullptr, nullptr);
+    k_root_h<false><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph.n_ngb, ph.h_maxit, cnt, rl, list, gcount, counts, fb_list,
+                                                        fb_count, nullptr);
     // one wave per handed-over particle, striding over the count left on the device
     k_solve_h_wave<<<kWaveBlocks, 64, 0, s>>>(a, td, tab, pos, ph, cnt, fb_list, fb_count, rl, list, gcount,
                                               counts, fb2_list, fb2_count, nullptr);
@@ -1737,6 +1819,8 @@ void launch_solve_h_active(const PassArrays& a, const TreeDesc& td, const int2* 
     launch_fill_u64(1, fb2_count, 0ull, s);
     k_solve_h<true><<<blocks_of(a.n, 256), 256, 0, s>>>(a, td, tab, pos, ph, cnt, rl, list, gcount, counts,
                                                         fb_list, fb_count, mode, pad);
+    k_root_h<true><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph.n_ngb, ph.h_maxit, cnt, rl, list, gcount, counts, fb_list,
+                                                       fb_count, mode);
     k_solve_h_wave<<<kWaveBlocks, 64, 0, s>>>(a, td, tab, pos, ph, cnt, fb_list, fb_count, rl, list, gcount,
                                               counts, fb2_list, fb2_count, pad);
     k_solve_h_fallback<<<kFallbackWaves, 64, 0, s>>>(a, td, tab, pos, ph, cnt, fb2_list, fb2_count, list, gcount,

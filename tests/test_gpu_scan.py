@@ -35,13 +35,17 @@ def _set(kind, n, seed):
                       u=np.full(n, 1.5), gamma=5.0 / 3.0, box=box, periodic=per)
 
 
-@pytest.mark.parametrize("kind,n", [("uniform", 300), ("uniform", 70001), ("slab", 66000), ("clumps", 2500),
-                                    ("clumps", 70003)])
-def test_lists_and_kernel_lengths_equal_brute_force(kind, n):
+# n_ngb 55 and 100: about 64 and 120 radii a particle, up to and past what the root kernel keeps in registers
+@pytest.mark.parametrize("kind,n,n_ngb", [("uniform", 300, 32.0), ("uniform", 70001, 32.0), ("slab", 66000, 32.0),
+                                          ("clumps", 2500, 32.0), ("clumps", 70003, 32.0), ("slab", 40009, 55.0),
+                                          ("uniform", 40009, 100.0)])
+def test_lists_and_kernel_lengths_equal_brute_force(kind, n, n_ngb):
+    import dataclasses
+
     import torch
 
     from paper_1712_01294_amd import mfm
-    w = _set(kind, n, W.SEED_BASE + 700 + n)
+    w = dataclasses.replace(_set(kind, n, W.SEED_BASE + 700 + n), n_ngb=n_ngb)
     ctx = mfm.Context(mfm.config_of(w, max_ngb=4096), n)
     st = mfm.State.from_arrays(w.arrays())
     ctx.build_neighbours(st)
