@@ -481,7 +481,7 @@ static mfm_status do_solve_h(mfm_ctx* c, mfm_particles* p, hipStream_t s) {
     if (c->n_tree != p->n) return fail(c, MFM_E_STATE, "mfm_build_neighbours must run on these particles first");
     PassArrays a = arrays_of(p);
     const auto ev = clock_take(c, MFM_KERNEL_SOLVE_H);
-    launch_solve_h(a, c->td, c->tab, c->pos, c->ph, c->cnt, c->rl, c->list, c->gcount, c->counts,
+    launch_solve_h(a, c->td, c->tab, c->pos, c->keys, c->ph, c->cnt, c->rl, c->list, c->gcount, c->counts,
                    c->fb_list, c->fb_count, c->fb2_list, c->fb2_count, ev.first, ev.second, s);
     c->have_h = 1;
     c->have_grad = c->have_flux = 0;
@@ -1035,7 +1035,7 @@ static mfm_status do_pass_active(mfm_ctx* c, mfm_particles* q, const long long* 
     PassArrays a = arrays_of(q);
     launch_hier_modes((int)n, q->x, q->y, q->z, q->H, bins, lmin, c->td, c->tab_len, c->hmarks, c->hmode,
                       c->gcount, c->counts, s);
-    launch_solve_h_active(a, c->td, c->tab, c->pos, c->ph, c->cnt, c->hmode, c->hmoved + n, c->rl, c->list,
+    launch_solve_h_active(a, c->td, c->tab, c->pos, c->keys, c->ph, c->cnt, c->hmode, c->hmoved + n, c->rl, c->list,
                           c->gcount, c->counts, c->fb_list, c->fb_count, c->fb2_list, c->fb2_count, s);
     launch_gradients_active(a, c->ph, c->hmode, c->hhome, c->gcount, c->counts, c->list, c->tails, c->prim, c->rec,
                             c->cnt, s);

@@ -115,6 +115,103 @@ __device__ __forceinline__ double min_image(double d, double L, int periodic) {
     return d;
 }
 
+// ------------------------------------------------------------ wave collectives
+// All 64 lanes participate.  Exchanges go through lane permutes of the vector
+// ALU (halves, rows of 16, rotations within a row, quads), not through LDS: six
+// dependent LDS permutes per 32 bits cost a reduction some 600 cycles, and a
+// scan pass takes eight reductions and a prefix sum per 64 cells.  The pairing
+// is that of a butterfly over distances 32, 16, 8, 4, 2, 1 (after the step over
+// 8 a row's lanes hold equal values 8 apart, so a rotation by 4 gives the value
+// of the lane 4 across), so sums take the same order on every lane.
+__device__ __forceinline__ void swap_halves(unsigned& a, unsigned& b) {   // upper half of a <-> lower half of b
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+__device__ __forceinline__ void swap_rows(unsigned& a, unsigned& b) {     // odd rows of a <-> even rows of b
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+template <int CTRL>
+__device__ __forceinline__ unsigned lane_move(unsigned v) {
+    return (unsigned)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
+}
+
+template <typename T>
+struct Words {
+    static constexpr int n = sizeof(T) / 4;
+    unsigned w[n];
+    __device__ __forceinline__ static Words of(T v) { return __builtin_bit_cast(Words, v); }
+    __device__ __forceinline__ T value() const { return __builtin_bit_cast(T, *this); }
+};
+
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_reduce(T v, Op op) {
+    using W = Words<T>;
+    W a = W::of(v), b = a;
+#pragma unroll
+    for (int k = 0; k < W::n; k++) swap_halves(a.w[k], b.w[k]);
+    a = b = W::of(op(a.value(), b.value()));
+#pragma unroll
+    for (int k = 0; k < W::n; k++) swap_rows(a.w[k], b.w[k]);
+    a = W::of(op(a.value(), b.value()));
+#pragma unroll
+    for (int k = 0; k < W::n; k++) b.w[k] = lane_move<0x128>(a.w[k]);   // row rotated by 8
+    a = W::of(op(a.value(), b.value()));
+#pragma unroll
+    for (int k = 0; k < W::n; k++) b.w[k] = lane_move<0x124>(a.w[k]);   // by 4
+    a = W::of(op(a.value(), b.value()));
+#pragma unroll
+    for (int k = 0; k < W::n; k++) b.w[k] = lane_move<0x4e>(a.w[k]);    // quad 2 3 0 1
+    a = W::of(op(a.value(), b.value()));
+#pragma unroll
+    for (int k = 0; k < W::n; k++) b.w[k] = lane_move<0xb1>(a.w[k]);    // quad 1 0 3 2
+    return op(a.value(), b.value());
+}
+
+__device__ __forceinline__ double wave_sum_d(double v) {
+    return wave_reduce(v, [](double a, double b) { return a + b; });
+}
+__device__ __forceinline__ double wave_min_d(double v) {
+    return wave_reduce(v, [](double a, double b) { return fmin(a, b); });
+}
+__device__ __forceinline__ double wave_max_d(double v) {
+    return wave_reduce(v, [](double a, double b) { return fmax(a, b); });
+}
+__device__ __forceinline__ int wave_min_i(int v) {
+    return wave_reduce(v, [](int a, int b) { return min(a, b); });
+}
+__device__ __forceinline__ int wave_max_i(int v) {
+    return wave_reduce(v, [](int a, int b) { return max(a, b); });
+}
+
+// inclusive prefix of op over the lanes, `none` its neutral value
+template <typename Op>
+__device__ __forceinline__ int wave_prefix(int v, int none, Op op) {
+    v = op(v, __builtin_amdgcn_update_dpp(none, v, 0x111, 0xf, 0xf, false));   // from 1, 2, 4, 8 lanes below, in the row
+    v = op(v, __builtin_amdgcn_update_dpp(none, v, 0x112, 0xf, 0xf, false));
+    v = op(v, __builtin_amdgcn_update_dpp(none, v, 0x114, 0xf, 0xf, false));
+    v = op(v, __builtin_amdgcn_update_dpp(none, v, 0x118, 0xf, 0xf, false));
+    v = op(v, __builtin_amdgcn_update_dpp(none, v, 0x142, 0xa, 0xf, false));   // last lane of rows 0, 2 to rows 1, 3
+    v = op(v, __builtin_amdgcn_update_dpp(none, v, 0x143, 0xc, 0xf, false));   // lane 31 to the upper half
+    return v;
+}
+__device__ __forceinline__ int wave_prefix_sum(int v) {
+    return wave_prefix(v, 0, [](int a, int b) { return a + b; });
+}
+__device__ __forceinline__ int wave_prefix_max(int v) {
+    return wave_prefix(v, -1, [](int a, int b) { return max(a, b); });
+}
+
+// a value known to be equal on all lanes, moved to scalar registers
+__device__ __forceinline__ double uniform_d(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffll));
+    const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
 // ------------------------------------------------- wave-cooperative cell scan
 // A group of lanes (Morton neighbours with similar trial radii) scans the union
 // of their neighbourhoods together: the cells of one table level whose boxes
@@ -156,12 +253,15 @@ __device__ __forceinline__ unsigned long long dilated_sub(unsigned long long x, 
     return (x - y) & mask;
 }
 
-// per-wave LDS of the cell enumeration
+// per-wave LDS of the cell enumeration: per axis and offset t = 0..63 from the
+// range's first cell, the key bits of the cell coordinate with its periodic
+// image in the top bits (2 per axis: shift + 1 in box sides), and its squared
+// distance from the box (rounded down)
+constexpr int kImageBit = 58;
 struct ScanLds {
-    int excl[kWave];        // exclusive prefix of the batch cells' particle counts
-    int start[kWave];       // first particle of each batch cell
-    int image[kWave];       // periodic image of each batch cell: 2 bits per axis, shift + 1 in box sides
-    unsigned long long key[3][kWave];   // key bits of cell coordinate a + t, t = 0..63, per axis
+    unsigned long long key[3][kWave];
+    float dist2[3][kWave];
+    int owner[kWave];       // cell of the batch whose particles start at each slot of a chunk, or -1
 };
 
 // per-wave LDS of the group scan: the staged candidates, kStage at a time
@@ -232,13 +332,6 @@ union Frag {
     uint4v u;
     half8 h;
 };
-
-// (lower half of a, lower half of b) and (upper half of a, upper half of b)
-__device__ __forceinline__ void swap_halves(unsigned& a, unsigned& b) {
-    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-    a = r[0];
-    b = r[1];
-}
 
 // Fragments of 64 points, one per lane: k 0-7 in f0 and k 8-15 in f1 of the
 // lane's own point become the operands of points 0-31 (f0) and 32-63 (f1):
@@ -318,42 +411,52 @@ __device__ __forceinline__ void scan_cells(const TreeDesc& td, const int2* __res
     int L = td.bmax;
     while (L > 0 && fmin(td.cs[L][0], fmin(td.cs[L][1], td.cs[L][2])) < scale * Rq) L--;
     L = __builtin_amdgcn_readfirstlane(L);
-    int a[3], cnt[3], nc[3];
-    int wrap = 0;
+    int a[3], cnt[3], wrap;
+    // (a range wider than the tables takes the next coarser level)
+    for (;; L--) {
+        wrap = 0;
+        bool wide = false;
 #pragma unroll
-    for (int d = 0; d < 3; d++) {
-        const double s = td.cs[L][d];
-        nc[d] = td.ncell[L][d];
-        int lo = (int)floor((bmin[d] - Rq) / s);
-        int hi = (int)floor((bmax[d] + Rq) / s);
-        if (td.periodic[d]) {
-            if (hi - lo + 1 >= nc[d]) {
-                lo = 0;
-                hi = nc[d] - 1;
-                wrap |= 1 << d;
+        for (int d = 0; d < 3; d++) {
+            const double s = td.cs[L][d];
+            const int nc = td.ncell[L][d];
+            int lo = (int)floor((bmin[d] - Rq) / s);
+            int hi = (int)floor((bmax[d] + Rq) / s);
+            if (td.periodic[d]) {
+                if (hi - lo + 1 >= nc) {
+                    lo = 0;
+                    hi = nc - 1;
+                    wrap |= 1 << d;
+                }
+            } else {
+                lo = max(lo, 0);
+                hi = min(hi, nc - 1);
             }
-        } else {
-            lo = max(lo, 0);
-            hi = min(hi, nc[d] - 1);
+            a[d] = __builtin_amdgcn_readfirstlane(lo);
+            cnt[d] = __builtin_amdgcn_readfirstlane(hi - lo + 1);
+            wide |= cnt[d] > kWave;
         }
-        a[d] = __builtin_amdgcn_readfirstlane(lo);
-        cnt[d] = __builtin_amdgcn_readfirstlane(hi - lo + 1);
+        if (!wide || L == 0) break;
     }
     wrap = __builtin_amdgcn_readfirstlane(wrap);
     if (cnt[0] <= 0 || cnt[1] <= 0 || cnt[2] <= 0) return;
     const int ncells = cnt[0] * cnt[1] * cnt[2];
-    // key bits of the range's cell coordinates (modulo the cells per axis) for
-    // offsets 0..63 along each axis; a wider range deposits per lane
+    wave_lds_sync();
 #pragma unroll
     for (int d = 0; d < 3; d++) {
-        const int w = (a[d] + lane) & (nc[d] - 1);   // nc is a power of two
-        S.key[d][lane] = deposit_bits((unsigned)w, td.mask[L][d]);
+        const int nc = td.ncell[L][d], u = a[d] + lane;
+        // unwrapped cell coordinates stay within one box side of [0, nc)
+        const unsigned long long image = u < 0 ? 0 : u >= nc ? 2 : 1;
+        const double s = td.cs[L][d], clo = u * s;
+        const double g = (wrap >> d) & 1 ? 0.0 : fmax(0.0, fmax(clo - bmax[d], bmin[d] - (clo + s)));
+        S.key[d][lane] = deposit_bits((unsigned)u & (nc - 1), td.mask[L][d]) | (image << (kImageBit + 2 * d));
+        S.dist2[d][lane] = (float)(g * g) * 0.9999998f;
     }
     wave_lds_sync();
-    // slack for the rounding of cell edges and of the keys' quantisation
+    // slack for the rounding of cell edges, of the keys' quantisation and of the distances in FP32
     const double Rg = Rq * (1.0 + 1e-9) + 1e-12 * fmax(td.box[0], fmax(td.box[1], td.box[2]));
-    const double Rg2 = Rg * Rg;
-    const long long off = td.tab_off[L];
+    const float Rg2 = (float)(Rg * Rg) * 1.000001f;
+    const int2* __restrict__ cells = tab + td.tab_off[L];
     // cell coordinates from the flat index through FP32 reciprocals (exact for
     // the few thousand cells a scan covers)
     const float inv2 = 1.0f / (float)cnt[2], inv1 = 1.0f / (float)cnt[1];
@@ -365,65 +468,85 @@ __device__ __forceinline__ void scan_cells(const TreeDesc& td, const int2* __res
             const int tz = c - t * cnt[2];
             const int tx = (int)(((float)t + 0.5f) * inv1);
             const int ty = t - tx * cnt[1];
-            const int u[3] = {a[0] + tx, a[1] + ty, a[2] + tz};
-            double g2 = 0.0;
-            unsigned long long key = 0;
-#pragma unroll
-            for (int d = 0; d < 3; d++) {
-                const double s = td.cs[L][d];
-                const double clo = u[d] * s;
-                const double g = (wrap >> d) & 1 ? 0.0 : fmax(0.0, fmax(clo - bmax[d], bmin[d] - (clo + s)));
-                g2 += g * g;
-                // unwrapped cell coordinates stay within one box side of [0, nc)
-                int w = u[d], im = 1;
-                if (w < 0) {
-                    w += nc[d];
-                    im = 0;
-                } else if (w >= nc[d]) {
-                    w -= nc[d];
-                    im = 2;
-                }
-                img |= im << (2 * d);
-                key |= cnt[d] <= kWave ? S.key[d][u[d] - a[d]] : deposit_bits((unsigned)w, td.mask[L][d]);
-            }
-            if (g2 < Rg2) {
-                const int2 se = tab[off + (long long)key];
+            if (S.dist2[0][tx] + S.dist2[1][ty] + S.dist2[2][tz] < Rg2) {
+                const unsigned long long key = S.key[0][tx] | S.key[1][ty] | S.key[2][tz];
+                const int2 se = cells[key & ((1ull << kImageBit) - 1)];
                 st = se.x;
                 num = se.y - se.x;
+                img = (int)(key >> kImageBit);
             }
         }
-        int incl = num;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int v = __shfl_up(incl, o, kWave);
-            if (lane >= o) incl += v;
-        }
-        const int total = __builtin_amdgcn_readfirstlane(__shfl(incl, kWave - 1, kWave));
-        if (total == 0) continue;
-        S.excl[lane] = incl - num;
-        S.start[lane] = st;
-        S.image[lane] = img;
-        wave_lds_sync();
+        const int incl = wave_prefix_sum(num), excl = incl - num;
+        const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
         for (int t0 = 0; t0 < total; t0 += kWave) {
+            // each cell with particles in the chunk marks its first slot there;
+            // the last mark at or below a slot is the cell that holds it
+            S.owner[lane] = -1;
+            wave_lds_sync();
+            if (num > 0 && incl > t0 && excl < t0 + kWave) S.owner[max(excl - t0, 0)] = lane;
+            wave_lds_sync();
+            const int k = wave_prefix_max(S.owner[lane]);
             const int t = t0 + lane;
+            const int j = __shfl(st - excl, k, kWave) + t, im = __shfl(img, k, kWave);
             // lanes past the end hold a far-away point that no sphere reaches
             double4 q = make_double4(1e30, 1e30, 1e30, __longlong_as_double(-1ll));
             if (t < total) {
-                // the last batch cell whose prefix is <= t holds particle t
-                int k = 0;
-#pragma unroll
-                for (int step = kWave / 2; step > 0; step >>= 1)
-                    if (S.excl[k + step] <= t) k += step;
-                const int j = S.start[k] + (t - S.excl[k]);
                 const double4 p = pos[j];
-                const int im = S.image[k];   // shifts of -1, 0 or 1 box sides (the product is exact)
+                // shifts of -1, 0 or 1 box sides (the product is exact)
                 q = make_double4(p.x + (double)((im & 3) - 1) * td.box[0], p.y + (double)(((im >> 2) & 3) - 1) * td.box[1],
                                  p.z + (double)((im >> 4) - 1) * td.box[2], __longlong_as_double((long long)j));
             }
             chunk(q, t < total, min(kWave, total - t0), wrap);
+            wave_lds_sync();   // the next chunk overwrites the owners
         }
-        wave_lds_sync();   // the next batch overwrites the cell data
     }
+}
+
+// sqrt(x) for 0 <= x far from the ends of the exponent range (a squared
+// distance): the steps of the correctly rounded sqrt without its rescaling of
+// arguments below 2^-767
+__device__ __forceinline__ double sqrt_mid(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, x), h, g);
+    g = fma(fma(-g, g, x), h, g);
+    return x > 0.0 ? g : 0.0;
+}
+
+// The lanes one group scan serves: of the lanes that still need one, those with
+// a radius of at least kClassRatio times the largest, within kClassWindow times
+// that of the first of them on every axis; their box and largest radius.
+// Fewer, wider classes pay down to a quarter: each pass scans the union once,
+// and its narrow lanes' extra candidates cost less than passes of their own.
+constexpr double kClassRatio = 0.25;
+constexpr double kClassWindow = 2.0;
+struct ScanClass {
+    bool in;
+    double Rq, bmin[3], bmax[3];
+};
+__device__ __forceinline__ ScanClass scan_class(bool need, double R, const double xi[3]) {
+    ScanClass c;
+    const double Rref = uniform_d(wave_max_d(need ? R : 0.0));
+    const bool big = need && R >= kClassRatio * Rref;
+    const int leader = __builtin_amdgcn_readfirstlane(__ffsll((long long)__ballot(big)) - 1);
+    const double win = kClassWindow * Rref;
+    bool in = big;
+#pragma unroll
+    for (int d = 0; d < 3; d++) {
+        const double xl = uniform_d(__shfl(xi[d], leader, kWave));
+        in &= fabs(xi[d] - xl) <= win;
+    }
+    c.in = in;
+    c.Rq = uniform_d(wave_max_d(in ? R : 0.0));
+#pragma unroll
+    for (int d = 0; d < 3; d++) {
+        c.bmin[d] = uniform_d(wave_min_d(in ? xi[d] : INFINITY));
+        c.bmax[d] = uniform_d(wave_max_d(in ? xi[d] : -INFINITY));
+    }
+    return c;
 }
 
 // Tests every particle of every cell within Rq + pad of the box [bmin, bmax]
@@ -457,8 +580,8 @@ __device__ __forceinline__ void group_scan(const TreeDesc& td, const int2* __res
     int spans = 0;   // axes the scan spans whole
     auto drain = [&]() {
         wave_lds_sync();
-        constexpr int kGroups = kStage / kWave;
-        unsigned long long mk[kGroups] = {};
+        constexpr int kWords = kStage / 32;
+        unsigned mk[kWords] = {};   // bit 31 - b of word w: staged candidate 32 w + b
         int left = 0;
 #pragma unroll 1
         for (int g = 0; g < kStage; g += kWave) {
@@ -484,19 +607,21 @@ __device__ __forceinline__ void group_scan(const TreeDesc& td, const int2* __res
             }
             left += __popcll(m);
 #pragma unroll
-            for (int q = 0; q + 1 < kGroups; q++) mk[q] = mk[q + 1];
-            mk[kGroups - 1] = m;
+            for (int q = 0; q + 2 < kWords; q++) mk[q] = mk[q + 2];
+            mk[kWords - 2] = (unsigned)(m >> 32);
+            mk[kWords - 1] = (unsigned)m;
         }
-        int base = 0;
+        int base = -32;
+        unsigned cur = 0;
         while (left > 0) {
-            while (mk[0] == 0) {
+            while (cur == 0) {
+                cur = mk[0];
+                base += 32;
 #pragma unroll
-                for (int q = 0; q + 1 < kGroups; q++) mk[q] = mk[q + 1];
-                mk[kGroups - 1] = 0;
-                base += kWave;
+                for (int q = 0; q + 1 < kWords; q++) mk[q] = mk[q + 1];
             }
-            const int b = __builtin_clzll(mk[0]);
-            mk[0] &= ~(0x8000000000000000ull >> b);
+            const int b = __builtin_clz(cur);
+            cur &= 0x7fffffffu >> b;
             left--;
             const int k = base + b;
             const double r2 = sq_disp(make_double4(S.x[k], S.y[k], S.z[k], 0.0), xi, spans, td.box);
@@ -517,33 +642,6 @@ __device__ __forceinline__ void group_scan(const TreeDesc& td, const int2* __res
         ns += nb;
     });
     if (ns > 0) drain();
-}
-
-// wave-wide sum of doubles in a fixed order (all 64 lanes participate)
-__device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// a value known to be equal on all lanes, moved to scalar registers
-__device__ __forceinline__ double uniform_d(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffll));
-    const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
-// wave-wide min / max of doubles (all 64 lanes participate)
-__device__ __forceinline__ double wave_min_d(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ __forceinline__ double wave_max_d(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
 }
 
 }  // namespace mfm

@@ -47,7 +47,8 @@ void launch_pos4(int n, const double* x, const double* y, const double* z, doubl
 
 // pass.hip
 void launch_solve_h(const PassArrays& a, const TreeDesc& td, const int2* tab,
-                    const double4* pos, const Phys& ph, Counters* cnt, double* rl, int* list, int* gcount,
+                    const double4* pos, const unsigned long long* keys, const Phys& ph, Counters* cnt, double* rl,
+                    int* list, int* gcount,
                     int* counts, int* fb_list, unsigned long long* fb_count, int* fb2_list,
                     unsigned long long* fb2_count, hipEvent_t t0, hipEvent_t t1, hipStream_t s);
 // flux-list tail entries per particle held in its contiguous tail buffer
@@ -75,7 +76,7 @@ constexpr unsigned char kModeNone = 0, kModeSolve = 1, kModeKept = 2;
 // (the cell tables may be those of an earlier build, with particles moved by
 // at most *pad since: every scan reaches that much further)
 void launch_solve_h_active(const PassArrays& a, const TreeDesc& td, const int2* tab, const double4* pos,
-                           const Phys& ph, Counters* cnt, const unsigned char* mode, const double* pad, double* rl,
+                           const unsigned long long* keys, const Phys& ph, Counters* cnt, const unsigned char* mode, const double* pad, double* rl,
                            int* list, int* gcount, int* counts, int* fb_list, unsigned long long* fb_count,
                            int* fb2_list, unsigned long long* fb2_count, hipStream_t s);
 // (the new gradient matrices and limited gradients of the active particles, and

@@ -22,41 +22,15 @@ __device__ __forceinline__ int xcd_block() {
     return x * q + (x < r ? x : r) + slot;
 }
 
-__device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-__device__ __forceinline__ unsigned long long wave_max(unsigned long long v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        unsigned long long t = __shfl_xor(v, o, 64);
-        v = t > v ? t : v;
-    }
-    return v;
-}
-
-__device__ __forceinline__ int wave_min_i(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ __forceinline__ int wave_max_i(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
 __device__ __forceinline__ void count_add(unsigned long long* c, unsigned long long v) {
-    v = wave_sum(v);
+    v = wave_reduce(v, [](unsigned long long a, unsigned long long b) { return a + b; });
     if ((threadIdx.x & 63) == 0 && v) atomicAdd(c, v);
 }
 
 // the atomic is skipped when the counter already holds at least v (a stale
 // read only costs an atomic that changes nothing)
 __device__ __forceinline__ void count_max(unsigned long long* c, unsigned long long v) {
-    v = wave_max(v);
+    v = wave_reduce(v, [](unsigned long long a, unsigned long long b) { return a > b ? a : b; });
     if ((threadIdx.x & 63) == 0 && v && v > __atomic_load_n(c, __ATOMIC_RELAXED)) atomicMax(c, v);
 }
 
@@ -105,34 +79,33 @@ struct BlockCount {
     double vol;
 };
 
-__device__ BlockCount block_count(const TreeDesc& td, const int2* __restrict__ tab, const double xi[3], int l) {
-    unsigned long long dil[3][3];   // deposited keys of coordinates c-1, c, c+1 per axis
+// the level-l block around the cell of a particle with the (full-depth) key;
+// the level is the same on every lane
+__device__ BlockCount block_count(const TreeDesc& td, const int2* __restrict__ tab, unsigned long long key, int l) {
+    unsigned long long dil[3][3];   // key bits of coordinates c-1, c, c+1 per axis
     bool ok[3][3];
     int ncl[3];
+    const unsigned long long cell = key >> (td.ktot - td.kbits[l]);
 #pragma unroll
     for (int d = 0; d < 3; d++) {
         const int nc = td.ncell[l][d];
-        const int c = min(nc - 1, max(0, (int)floor(xi[d] / td.cs[l][d])));
         // the neighbours c - 1 and c + 1 by dilated subtraction and addition of
-        // the deposited 1 (wrapping modulo nc, which only periodic axes use)
+        // the lowest key bit of the axis (wrapping modulo nc, which only periodic
+        // axes use); c is 0 or nc - 1 where none or all of the axis's bits are set
         const unsigned long long m = td.mask[l][d];
         const unsigned long long one = m & (~m + 1);
-        const unsigned long long dc = deposit_bits((unsigned)c, m);
-        const unsigned long long dn[3] = {dilated_sub(dc, one, m), dc, dilated_add(dc, one, m)};
-        ncl[d] = 0;
-#pragma unroll
-        for (int o = 0; o < 3; o++) {
-            const int w = c + o - 1;
-            bool in = true;
-            if ((w < 0 || w >= nc) && !(td.periodic[d] && nc >= 3)) in = false;
-            if (nc < 3 && o != 1) in = false;   // fewer than 3 cells: count each once
-            ok[d][o] = in;
-            ncl[d] += in;
-            dil[d][o] = in ? dn[o] : 0ull;
-        }
+        const unsigned long long dc = cell & m;
+        dil[d][0] = dilated_sub(dc, one, m);
+        dil[d][1] = dc;
+        dil[d][2] = dilated_add(dc, one, m);
+        // fewer than 3 cells: count each once
+        ok[d][0] = nc >= 3 && (td.periodic[d] || dc != 0);
+        ok[d][1] = true;
+        ok[d][2] = nc >= 3 && (td.periodic[d] || dc != m);
+        ncl[d] = 1 + ok[d][0] + ok[d][2];
     }
     int cnt = 0;
-    const long long off = td.tab_off[l];
+    const int2* __restrict__ cells = tab + td.tab_off[l];
 #pragma unroll
     for (int ox = 0; ox < 3; ox++)
 #pragma unroll
@@ -141,36 +114,40 @@ __device__ BlockCount block_count(const TreeDesc& td, const int2* __restrict__ t
             for (int oz = 0; oz < 3; oz++) {
                 // cells outside an open side read cell 0 and count nothing
                 const bool in = ok[0][ox] && ok[1][oy] && ok[2][oz];
-                const int2 se = tab[off + (long long)(in ? (dil[0][ox] | dil[1][oy] | dil[2][oz]) : 0ull)];
+                const int2 se = cells[in ? (dil[0][ox] | dil[1][oy] | dil[2][oz]) : 0ull];
                 cnt += in ? se.y - se.x : 0;
             }
     return {(double)cnt, ncl[0] * td.cs[l][0] * ncl[1] * td.cs[l][1] * ncl[2] * td.cs[l][2]};
 }
 
-__device__ double cold_guess(const TreeDesc& td, const int2* __restrict__ tab, const double xi[3],
+// every lane of the wave takes part; the lanes with `want` get a guess
+__device__ double cold_guess(const TreeDesc& td, const int2* __restrict__ tab, unsigned long long key, bool want,
                              double n_ngb, long long n) {
     const double need = kColdCount;
     const double nbox = (double)n / (td.box[0] * td.box[1] * td.box[2]);
-    int l = td.bmax;
-    while (l > 0 && 27.0 * nbox * td.cs[l][0] * td.cs[l][1] * td.cs[l][2] < need) l--;
-    BlockCount b = block_count(td, tab, xi, l);
+    int l0 = td.bmax;
+    while (l0 > 0 && 27.0 * nbox * td.cs[l0][0] * td.cs[l0][1] * td.cs[l0][2] < need) l0--;
+    l0 = __builtin_amdgcn_readfirstlane(l0);
+    BlockCount b = {0.0, 0.0};
     BlockCount f = {-1.0, 0.0};   // the finer block (count < need), once known
-    if (b.count >= need) {
-        while (l < td.bmax) {
-            const BlockCount g = block_count(td, tab, xi, l + 1);
+    if (want) b = block_count(td, tab, key, l0);
+    bool finer = want && b.count >= need, coarser = want && !finer;
+    for (int l = l0 + 1; l <= td.bmax && __ballot(finer); l++)
+        if (finer) {
+            const BlockCount g = block_count(td, tab, key, l);
             if (g.count < need) {
                 f = g;
-                break;
+                finer = false;
+            } else {
+                b = g;
             }
-            b = g;
-            l++;
         }
-    } else {
-        while (l > 0 && b.count < need) {
+    for (int l = l0 - 1; l >= 0 && __ballot(coarser); l--)
+        if (coarser) {
             f = b;
-            b = block_count(td, tab, xi, --l);
+            b = block_count(td, tab, key, l);
+            coarser = b.count < need;
         }
-    }
     double vol = b.vol, count = fmax(b.count, 1.0);
     if (f.count >= 0.0 && b.count >= need && f.vol < b.vol) {
         // log count linear in log volume between the two blocks, at count = need
@@ -225,13 +202,6 @@ __device__ __forceinline__ bool newton_step(double f, double fp, double& lo, dou
 // cheaper for them than further group passes over a sparse class.
 constexpr double kColdPad = 1.05;   // scan radius over a cold guess
 constexpr double kWarmPad = 1.03;   // scan radius over the previous H
-// a scan pass takes the lanes with R >= kClassRatio Rref within kClassWindow Rref
-// of the first of them on every axis (Rref: the largest trial radius pending).
-// Fewer, wider classes pay down to a quarter: each pass scans the union once,
-// and its narrow lanes' extra candidates cost less than passes of their own.
-constexpr double kClassRatio = 0.25;
-constexpr double kClassWindow = 2.0;
-
 // Four waves per SIMD: 128 VGPRs, and the 37 KB of staged candidates per block
 // fit four times in the LDS of a compute unit.
 // With HIER (hierarchical steps with active subsets) only the particles of
@@ -241,8 +211,8 @@ constexpr double kClassWindow = 2.0;
 constexpr int kSolveWaves = 4;
 template <bool HIER>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves))) void k_solve_h(PassArrays a, TreeDesc td, const int2* __restrict__ tab,
-                                                  const double4* __restrict__ pos, Phys ph, Counters* cnt,
-                                                  double* __restrict__ rl, int* __restrict__ jl,
+                                                  const double4* __restrict__ pos, const unsigned long long* __restrict__ keys, Phys ph,
+                                                  Counters* cnt, double* __restrict__ rl, int* __restrict__ jl,
                                                   int* __restrict__ gcount, int* __restrict__ counts,
                                                   int* __restrict__ fb_list, unsigned long long* __restrict__ fb_count,
                                                   const unsigned char* __restrict__ mode, const double* __restrict__ pad) {
@@ -268,50 +238,42 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
         xi[2] = pi.z;
         guess = a.H[i];
         warm = guess > 0.0;
-        if (!warm) guess = cold_guess(td, tab, xi, ph.n_ngb, a.n);
+    }
+    if (__ballot(act && !warm)) {
+        const double g = cold_guess(td, tab, act ? keys[i] : 0ull, act && !warm, ph.n_ngb, a.n);
+        if (!warm) guess = g;
+    }
+    if (act) {
         R = (warm ? kWarmPad : kColdPad) * guess;
         if (R >= half) R = half * (1.0 - 1e-12);
     }
     // Weighted counts at R and at two trial lengths: below the guess (at it on a
-    // cold start) and at the scan radius again, formed from the guess; the radii
-    // below Sl are listed.
+    // cold start) and at the scan radius again, formed from the guess.
     const double Hg = R * (warm ? 1.0 / kWarmPad : 1.0 / kColdPad);
     const double Ht0 = warm ? 0.97 * Hg : Hg, Ht1 = (warm ? kWarmPad : kColdPad) * Hg;
-    const double Sl = warm ? R : Ht1;
     double sw = 0.0, st0 = 0.0, st1 = 0.0;
     int m = 0;   // radii met, listed while they fit
+    double* __restrict__ rp = rl + i;
+    int* __restrict__ jp = jl + i;
     bool need = act && R > 0.0;
     for (int pass = 0; pass < kWave; pass++) {
         if (__ballot(need) == 0) break;
-        // this pass: lanes within kClassRatio of the largest radius and close to the first such lane
-        const double Rref = uniform_d(wave_max_d(need ? R : 0.0));
-        const bool big = need && R >= kClassRatio * Rref;
-        const int leader = __builtin_amdgcn_readfirstlane(__ffsll((long long)__ballot(big)) - 1);
-        const double win = kClassWindow * Rref;
-        const double xl0 = uniform_d(__shfl(xi[0], leader, kWave)), xl1 = uniform_d(__shfl(xi[1], leader, kWave)),
-                     xl2 = uniform_d(__shfl(xi[2], leader, kWave));
-        const bool cls = big && fabs(xi[0] - xl0) <= win && fabs(xi[1] - xl1) <= win && fabs(xi[2] - xl2) <= win;
-        const double Rq = uniform_d(wave_max_d(cls ? R : 0.0));
-        double bmin[3], bmax[3];
-        for (int d = 0; d < 3; d++) {
-            bmin[d] = uniform_d(wave_min_d(cls ? xi[d] : INFINITY));
-            bmax[d] = uniform_d(wave_max_d(cls ? xi[d] : -INFINITY));
-        }
+        const ScanClass cl = scan_class(need, R, xi);
         const double iR = 1.0 / R, iT0 = 1.0 / Ht0, iT1 = 1.0 / Ht1;
-        group_scan(td, tab, pos, S, lane, bmin, bmax, Rq, HIER ? *pad : 0.0, xi, R * R, cls, [&](int j, double r2) {
-            const double r = sqrt(r2);
-            if (r < Sl) {
-                if (m < cap) {
-                    rl[(long long)m * n + i] = r;
-                    jl[(long long)m * n + i] = j;
-                }
-                m++;
+        group_scan(td, tab, pos, S, lane, cl.bmin, cl.bmax, cl.Rq, HIER ? *pad : 0.0, xi, R * R, cl.in, [&](int j, double r2) {
+            const double r = sqrt_mid(r2);
+            if (m < cap) {
+                *rp = r;
+                *jp = j;
             }
+            rp += n;
+            jp += n;
+            m++;
             sw += spline_w(r * iR);
             st0 += spline_w(r * iT0);
             st1 += spline_w(r * iT1);
         });
-        need = need && !cls;
+        need = need && !cl.in;
     }
     // A bracket with every radius below it listed is narrowed by the trial counts
     // (summed in the order of the Newton sums, so the signs agree).  Newton starts
@@ -319,7 +281,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
     // the density scaling of the upper end.
     const double neff = c32 * sw;
     double lo = 0.0, hi = R, neff_hi = neff, fa = NAN;
-    bool found = act && neff >= ph.n_ngb && m <= cap;
+    const bool found = act && neff >= ph.n_ngb && m <= cap;
     if (found) {
         const double f0 = add_rn(mul_rn(c32, st0), -ph.n_ngb), f1 = add_rn(mul_rn(c32, st1), -ph.n_ngb);
         if (Ht1 < hi) {
@@ -330,7 +292,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
             if (f0 >= 0.0) hi = Ht0, neff_hi = f0 + ph.n_ngb;
             else lo = Ht0, fa = f0;
         }
-        found = !(hi > Sl);   // else the root lies above the listed radii
     }
     if (found) {
         // Newton's start and bracket, for the root kernel
@@ -359,8 +320,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
             // bracketed, but too many radii to keep: just above the estimated root
             Rn = fmax(lo + 0.25 * (hi - lo), fmin(1.05 * R * cbrt(ph.n_ngb / neff), R * cbrt(0.8 * cap / m)));
             if (!(Rn < hi)) Rn = 0.5 * (lo + hi);
-        } else if (hi > Sl) {
-            Rn = hi;
         }
         const unsigned long long slot = atomicAdd(fb_count, 1ull);
         if (slot < (unsigned long long)a.n) fb_list[slot] = i;
@@ -812,7 +771,7 @@ __global__ __launch_bounds__(64) void k_solve_h_fallback(PassArrays a, TreeDesc 
 // gather set r < H at the current positions with the scan and the distance
 // test of the kernel-length solve, so that both particles of a pair decide on
 // the same distance.  The lanes of a wave (Morton neighbours) scan together
-// over the largest of their radii.
+// in the classes of the kernel-length scan.
 __global__ __launch_bounds__(256) void k_gather_kept(PassArrays a, TreeDesc td, const int2* __restrict__ tab,
                                                      const double4* __restrict__ pos, Phys ph,
                                                      const unsigned char* __restrict__ mode, const double* __restrict__ pad,
@@ -836,21 +795,20 @@ __global__ __launch_bounds__(256) void k_gather_kept(PassArrays a, TreeDesc td, 
     }
     // scanned a little beyond H, so that no r < H is lost to the rounding of r^2
     const double Rs = H * (1.0 + 1e-9);
-    const double Rq = uniform_d(wave_max_d(sel ? Rs : 0.0));
-    double bmin[3], bmax[3];
-    for (int d = 0; d < 3; d++) {
-        bmin[d] = uniform_d(wave_min_d(sel ? xi[d] : INFINITY));
-        bmax[d] = uniform_d(wave_max_d(sel ? xi[d] : -INFINITY));
-    }
     const int cap = ph.max_ngb;
     int c = 0;
-    group_scan(td, tab, pos, S, lane, bmin, bmax, Rq, *pad, xi, Rs * Rs, sel, [&](int j, double r2) {
-        const double r = sqrt(r2);
-        if (r < H && j != i) {
-            if (c < cap) jl[(long long)c * n + i] = j;
-            c++;
-        }
-    });
+    bool need = sel && Rs > 0.0;
+    for (int pass = 0; pass < kWave && __ballot(need); pass++) {
+        const ScanClass cl = scan_class(need, Rs, xi);
+        group_scan(td, tab, pos, S, lane, cl.bmin, cl.bmax, cl.Rq, *pad, xi, Rs * Rs, cl.in, [&](int j, double r2) {
+            const double r = sqrt_mid(r2);
+            if (r < H && j != i) {
+                if (c < cap) jl[(long long)c * n + i] = j;
+                c++;
+            }
+        });
+        need = need && !cl.in;
+    }
     if (sel) {
         gcount[i] = min(c, cap);
         counts[i] = c;   // beyond cap: an overflow, counted when the tails are sorted
@@ -1778,13 +1736,14 @@ static int blocks_of(int n, int b) { return (n + b - 1) / b; }
 constexpr int kFallbackWaves = 1024;
 
 void launch_solve_h(const PassArrays& a, const TreeDesc& td, const int2* tab,
-                    const double4* pos, const Phys& ph, Counters* cnt, double* rl, int* list, int* gcount,
+                    const double4* pos, const unsigned long long* keys, const Phys& ph, Counters* cnt, double* rl, int* list,
+                    int* gcount,
                     int* counts, int* fb_list, unsigned long long* fb_count, int* fb2_list,
                     unsigned long long* fb2_count, hipEvent_t t0, hipEvent_t t1, hipStream_t s) {
     launch_fill_u64(1, fb_count, 0ull, s);
     launch_fill_u64(1, fb2_count, 0ull, s);
     if (t0) hipEventRecord(t0, s);
-    k_solve_h<false><<<blocks_of(a.n, 256), 256, 0, s>>>(a, td, tab, pos, ph, cnt, rl, list, gcount, counts,
+    k_solve_h<false><<<blocks_of(a.n, 256), 256, 0, s>>>(a, td, tab, pos, keys, ph, cnt, rl, list, gcount, counts,
                                                          fb_list, fb_count, nullptr, nullptr);
     k_root_h<false><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph.n_ngb, ph.h_maxit, cnt, rl, list, gcount, counts, fb_list,
                                                         fb_count, nullptr);
@@ -1812,12 +1771,12 @@ void launch_gradients(const PassArrays& a, const Phys& ph, const int* gcount, in
 }
 
 void launch_solve_h_active(const PassArrays& a, const TreeDesc& td, const int2* tab, const double4* pos,
-                           const Phys& ph, Counters* cnt, const unsigned char* mode, const double* pad, double* rl,
+                           const unsigned long long* keys, const Phys& ph, Counters* cnt, const unsigned char* mode, const double* pad, double* rl,
                            int* list, int* gcount, int* counts, int* fb_list, unsigned long long* fb_count,
                            int* fb2_list, unsigned long long* fb2_count, hipStream_t s) {
     launch_fill_u64(1, fb_count, 0ull, s);
     launch_fill_u64(1, fb2_count, 0ull, s);
-    k_solve_h<true><<<blocks_of(a.n, 256), 256, 0, s>>>(a, td, tab, pos, ph, cnt, rl, list, gcount, counts,
+    k_solve_h<true><<<blocks_of(a.n, 256), 256, 0, s>>>(a, td, tab, pos, keys, ph, cnt, rl, list, gcount, counts,
                                                         fb_list, fb_count, mode, pad);
     k_root_h<true><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph.n_ngb, ph.h_maxit, cnt, rl, list, gcount, counts, fb_list,
                                                        fb_count, mode);
