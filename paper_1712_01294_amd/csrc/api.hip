@@ -513,7 +513,7 @@ static mfm_status do_fluxes(mfm_ctx* c, mfm_particles* p, hipStream_t s) {
     PassArrays a = arrays_of(p);
     const auto ev = clock_take(c, MFM_KERNEL_FLUXES);
     if (ev.first) hipEventRecord(ev.first, s);
-    launch_fluxes(a, c->ph, c->counts, c->list, c->rec_mixed, mfv, c->rec, c->cnt, s);
+    launch_fluxes(a, c->ph, c->counts, c->list, c->rec_mixed, mfv, c->rec, c->prim, c->cnt, s);
     if (ev.second) hipEventRecord(ev.second, s);
     c->have_flux = 1;
     c->last = s;
@@ -1017,7 +1017,7 @@ static mfm_status do_fluxes_levels(mfm_ctx* c, mfm_particles* p, const long long
                                    const long long* home, hipStream_t s) {
     if (!c->have_grad || c->n_tree != p->n) return fail(c, MFM_E_STATE, "mfm_gradients must run first");
     PassArrays a = arrays_of(p);
-    launch_fluxes_levels(a, c->ph, c->counts, c->list, c->rec, c->cnt, bins, lmin, nlev, c->lev, home, s);
+    launch_fluxes_levels(a, c->ph, c->counts, c->list, c->rec, c->prim, c->cnt, bins, lmin, nlev, c->lev, home, s);
     c->have_flux = 1;
     c->last = s;
     return launched(c, "hydro_fluxes (levels)");

@@ -212,6 +212,61 @@ __device__ __forceinline__ double uniform_d(double v) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
+// order the LDS traffic of one wave (lanes read what other lanes wrote)
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// ------------------------------------------------------- gathers by lane teams
+// The first C 16-byte chunks of one record per lane, lane l's at base + STRIDE
+// j(l), through LDS.  A load whose 64 lanes each read 16 bytes of a record of their own looks
+// up 64 cache lines, and the L1 takes about one a clock: with 16 such loads per
+// neighbour the FP64 flux kernel spent 1.77 ms of its 1.80 on the lookups
+// (2.1M particles).  Here C neighbouring lanes read one record's chunks side by
+// side, straight into LDS (64 / C records per load instruction), and each lane
+// reads its record back from there.  Chunk c of lane r's record sits at
+// position (c + r) mod C, so the lanes' reads of one chunk fall in different
+// banks.  C is a power of two.
+template <int C>
+struct TeamLds {
+    uint4 rec[kWave * C];
+    int idx[kWave];
+};
+
+// LDS reads issued so far have returned / vector memory operations have completed
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xc07f); }
+__device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+
+// starts the loads of records j (one per lane, all 64 lanes); the earlier
+// records' reads must have returned
+template <int STRIDE, int C>
+__device__ __forceinline__ void team_load(TeamLds<C>& S, const void* __restrict__ base, int j, int lane) {
+    constexpr int kTeams = kWave / C;
+    S.idx[(lane % kTeams) * C + lane / kTeams] = j;
+    wave_lds_sync();
+    const int team = lane / C, p = lane % C;
+    int js[C];
+#pragma unroll
+    for (int q = 0; q < C; q++) js[q] = S.idx[team * C + q];
+    wave_lds_sync();
+    wait_lds();
+#pragma unroll
+    for (int q = 0; q < C; q++) {
+        const int r = kTeams * q + team;
+        const char* g = (const char*)base + (size_t)(unsigned)js[q] * STRIDE + ((p - r) & (C - 1)) * 16;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                         (__attribute__((address_space(3))) void*)(S.rec + q * kWave), 16, 0, 0);
+    }
+}
+
+// chunk c of the lane's record, after wait_vmem
+template <int C>
+__device__ __forceinline__ uint4 team_chunk(const TeamLds<C>& S, int c, int lane) {
+    return S.rec[lane * C + ((c + lane) & (C - 1))];
+}
+
 // ------------------------------------------------- wave-cooperative cell scan
 // A group of lanes (Morton neighbours with similar trial radii) scans the union
 // of their neighbourhoods together: the cells of one table level whose boxes
@@ -271,13 +326,6 @@ struct GroupLds {
     int j[kStage];
     ScanLds cells;
 };
-
-// order the LDS traffic of one wave (lanes read what other lanes wrote)
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 __device__ __forceinline__ double sq_disp(const double4& q, const double xi[3], int wrap, const double box[3]) {
     double d0 = q.x - xi[0], d1 = q.y - xi[1], d2 = q.z - xi[2];

@@ -57,13 +57,13 @@ void launch_gradients(const PassArrays& a, const Phys& ph, const int* gcount, in
                       int mixed, double4* prim, void* rec, Counters* cnt, hipEvent_t t0, hipEvent_t t1,
                       hipStream_t s);
 void launch_fluxes(const PassArrays& a, const Phys& ph, const int* counts, const int* list,
-                   int mixed, int mfv, const void* rec, Counters* cnt, hipStream_t s);
+                   int mixed, int mfv, const void* rec, const double4* prim, Counters* cnt, hipStream_t s);
 // hierarchical steps: the pairs of level >= lmin (level = the finer bin of the
 // two), their per-level sums into lev[(l * 4 + c) * n + i] (FP64 records, MFM)
 constexpr int kMaxBin = 7;
 // (particle i's sums at column home[i] of lev; home null: column i)
 void launch_fluxes_levels(const PassArrays& a, const Phys& ph, const int* counts, const int* list, const void* rec,
-                          Counters* cnt, const long long* bin, int lmin, int nlev, double* lev,
+                          const double4* prim, Counters* cnt, const long long* bin, int lmin, int nlev, double* lev,
                           const long long* home, hipStream_t s);
 
 // hierarchical steps with active subsets (FP64 records, MFM): a particle's

@@ -1548,114 +1548,162 @@ struct Levels {
     const long long* home;   // column of lev per particle (null: the particle's index)
 };
 
+// LDS of one wave's record gathers: the FP64 record (256 B), or the FP32 record
+// (128 B) and the FP64 position from the packed neighbour record
+template <typename T>
+struct FluxLds;
+template <>
+struct FluxLds<double> {
+    TeamLds<16> rec;
+};
+template <>
+struct FluxLds<float> {
+    TeamLds<8> rec;
+    TeamLds<2> pos;
+};
+
 template <typename T, bool MFV, bool LIM, bool LEV = false>
 __device__ __forceinline__ void fluxes_body(const PassArrays& a, const Phys& ph, const int* __restrict__ counts,
                                             const int* __restrict__ list, const T* __restrict__ rec,
-                                            Counters* cnt, Levels lv = Levels{nullptr, 0, 0, nullptr, nullptr}) {
+                                            const double4* __restrict__ prim, Counters* cnt,
+                                            Levels lv = Levels{nullptr, 0, 0, nullptr, nullptr}) {
     cnt = counter_copy(cnt);
-    const int i = xcd_block() * 256 + threadIdx.x;
+    __shared__ FluxLds<T> S;
+    const int lane = threadIdx.x;
+    const int i = xcd_block() * kWave + lane;
     const bool act = i < a.n;
+    const long long n = a.n;
+    const int self = act ? i : a.n - 1;   // a record to load where a lane has no pair
     unsigned long long nfall = 0, nclamp = 0, nonfin = 0;
-    if (act) {
-        const long long n = a.n;
-        T ri[32];
-        // in the levelled pass most particles of a partial boundary have no
-        // list: their record is not read (its values only enter pairs)
-        if (LEV && counts[i] == 0) {
+    const int cnum = act ? counts[i] : 0;
+    T ri[32];
+    // in the levelled pass most particles of a partial boundary have no
+    // list: their record is not read (its values only enter pairs)
+    if (cnum == 0 && (LEV || !act)) {
 #pragma unroll
-            for (int q = 0; q < 32; q++) ri[q] = T(0);
-        } else {
-            load_rec<T>(rec, i, ri);
-        }
-        const double xi[3] = {a.x[i], a.y[i], a.z[i]};
-        const double vi[3] = {(double)ri[R_V0], (double)ri[R_V0 + 1], (double)ri[R_V0 + 2]};
-        const double ci = (double)ri[R_C];
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        double accm = 0.0;
-        double vs = 0.0;
-        const T gam = (T)ph.gamma;
-        const int cnum = counts[i];
-        int bi = 0;
-        long long li = i;
-        double lacc[kLevWin][4];
-        if (LEV) {
+        for (int q = 0; q < 32; q++) ri[q] = T(0);
+    } else {
+        load_rec<T>(rec, i, ri);
+    }
+    double xi[3] = {0.0, 0.0, 0.0};
+    if (act) {
+        xi[0] = a.x[i];
+        xi[1] = a.y[i];
+        xi[2] = a.z[i];
+    }
+    const double vi[3] = {(double)ri[R_V0], (double)ri[R_V0 + 1], (double)ri[R_V0 + 2]};
+    const double ci = (double)ri[R_C];
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    double accm = 0.0;
+    double vs = 0.0;
+    const T gam = (T)ph.gamma;
+    int bi = 0;
+    long long li = i;
+    double lacc[kLevWin][4];
+    if (LEV) {
+        if (act) {
             bi = (int)lv.bin[i];
             if (lv.home) li = lv.home[i];
+        }
 #pragma unroll
-            for (int w = 0; w < kLevWin; w++)
+        for (int w = 0; w < kLevWin; w++)
 #pragma unroll
-                for (int c = 0; c < 4; c++) lacc[w][c] = 0.0;
+            for (int c = 0; c < 4; c++) lacc[w][c] = 0.0;
+        if (act)
             for (int l = max(lv.lmin, bi + kLevWin); l < lv.nlev; l++)
                 for (int c = 0; c < 4; c++) lv.lev[((long long)l * 4 + c) * n + li] = 0.0;
+    }
+    // One pair per lane and step, the wave running as far as its longest list:
+    // while a pair is evaluated the next one's record is on its way to LDS, and
+    // the index of the one after to a register.  A pair that is not due in the
+    // levelled pass costs its bin alone (no flux, no signal speed: the last
+    // boundary of a system step has every pair due, so the signal speeds it
+    // leaves are complete), and a step without a due pair loads no records.
+    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i(cnum));
+    auto entry = [&](int k) { return k < cnum ? list[(long long)k * n + i] : -1; };
+    auto level = [&](int j) { return j >= 0 ? max(bi, (int)lv.bin[j]) : -1; };
+    auto is_due = [&](int j, int l) { return j >= 0 && (!LEV || l >= lv.lmin); };
+    auto start = [&](bool on, int j) {
+        if (LEV && !__ballot(on)) return;
+        const int jr = on ? j : self;
+        team_load<32 * sizeof(T)>(S.rec, rec, jr, lane);
+        if constexpr (sizeof(T) == 4) team_load<128>(S.pos, prim, jr, lane);
+    };
+    int j = entry(0), jn = entry(1);
+    int lj = LEV ? level(j) : 0;
+    bool due = is_due(j, lj);
+    if (kmax > 0) start(due, j);
+    for (int k = 0; k < kmax; k++) {
+        T rj[32];
+        double xj[3];
+        wait_vmem();
+        wave_lds_sync();
+#pragma unroll
+        for (int c = 0; c < (int)sizeof(T) * 2; c++) {
+            const uint4 u = team_chunk(S.rec, c, lane);
+            __builtin_memcpy(rj + c * (16 / sizeof(T)), &u, 16);
         }
-        // the next list entry is loaded one pair ahead, so the record loads of
-        // a pair do not wait for its index
-        int jn = cnum > 0 ? list[i] : 0;
-        for (int k = 0; k < cnum; k++) {
-            const int j = jn;
-            if (k + 1 < cnum) jn = list[(long long)(k + 1) * n + i];
-            int lj = 0;
-            if (LEV) {
-                // a pair that is not due costs its bin alone: no record, no flux,
-                // no signal speed (the last boundary of a system step has every
-                // pair due, so the signal speeds it leaves are complete); with
-                // every level due the record load does not wait for the bin
-                lj = max(bi, (int)lv.bin[j]);
-                if (lv.lmin > 0 && lj < lv.lmin) continue;
-            }
-            T rj[32];
-            load_rec<T>(rec, j, rj);
-            double xj[3];
-            if (sizeof(T) == 8) {
-                xj[0] = (double)rj[0];
-                xj[1] = (double)rj[1];
-                xj[2] = (double)rj[2];
+        if constexpr (sizeof(T) == 8) {
+            xj[0] = (double)rj[0];
+            xj[1] = (double)rj[1];
+            xj[2] = (double)rj[2];
+        } else {
+            const uint4 u = team_chunk(S.pos, 0, lane), v = team_chunk(S.pos, 1, lane);
+            __builtin_memcpy(xj, &u, 16);
+            __builtin_memcpy(xj + 2, &v, 8);
+        }
+        const int jc = j, lc = lj;
+        const bool on = due;
+        j = jn;
+        lj = LEV ? level(j) : 0;
+        due = is_due(j, lj);
+        wave_lds_sync();
+        wait_lds();
+        if (k + 1 < kmax) start(due, j);
+        jn = entry(k + 2);
+        if (!on) continue;
+        double dij[3];
+        displacement(ph, xi, xj[0], xj[1], xj[2], dij);   // x_j - x_i
+        const double r = sqrt(dij[0] * dij[0] + dij[1] * dij[1] + dij[2] * dij[2]);
+        const bool iL = i < jc;
+        // signal speed over the flux neighbours (the due ones in the levelled pass)
+        auto signal = [&]() {
+            const double cj = (double)rj[R_C];
+            const double proj = -((vi[0] - (double)rj[R_V0]) * dij[0] + (vi[1] - (double)rj[R_V0 + 1]) * dij[1] +
+                                  (vi[2] - (double)rj[R_V0 + 2]) * dij[2]) / r;
+            vs = fmax(vs, ci + cj - fmin(proj, 0.0));
+        };
+        // canonical displacement x_R - x_L: the minimum image commutes with
+        // negation exactly, so both owners of the pair hold the same bits
+        const double sg = iL ? 1.0 : -1.0;
+        const T dT[3] = {(T)(sg * dij[0]), (T)(sg * dij[1]), (T)(sg * dij[2])};
+        PairOut<T> o = pair_flux<T, MFV, LIM>(ri, rj, iL, dT, (T)r, gam);
+        const double s = iL ? 1.0 : -1.0;
+        if (MFV) accm -= s * (double)o.Fm;
+        acc[0] -= s * (double)o.Fp[0];
+        acc[1] -= s * (double)o.Fp[1];
+        acc[2] -= s * (double)o.Fp[2];
+        acc[3] -= s * (double)o.FE;
+        nfall += o.fallback;
+        nclamp += o.clamp;
+        signal();
+        if (LEV) {
+            const double F[4] = {(double)o.Fp[0], (double)o.Fp[1], (double)o.Fp[2], (double)o.FE};
+            const int w = lc - bi;
+            if (w == 0) {   // both particles in one bin: most pairs
+#pragma unroll
+                for (int c = 0; c < 4; c++) lacc[0][c] = lacc[0][c] - s * F[c];
+            } else if (w < kLevWin) {
+#pragma unroll
+                for (int q = 1; q < kLevWin; q++)
+#pragma unroll
+                    for (int c = 0; c < 4; c++) lacc[q][c] = (q == w) ? lacc[q][c] - s * F[c] : lacc[q][c];
             } else {
-                xj[0] = a.x[j];
-                xj[1] = a.y[j];
-                xj[2] = a.z[j];
-            }
-            double dij[3];
-            displacement(ph, xi, xj[0], xj[1], xj[2], dij);   // x_j - x_i
-            const double r = sqrt(dij[0] * dij[0] + dij[1] * dij[1] + dij[2] * dij[2]);
-            const bool iL = i < j;
-            // signal speed over the flux neighbours (the due ones in the levelled pass)
-            auto signal = [&]() {
-                const double cj = (double)rj[R_C];
-                const double proj = -((vi[0] - (double)rj[R_V0]) * dij[0] + (vi[1] - (double)rj[R_V0 + 1]) * dij[1] +
-                                      (vi[2] - (double)rj[R_V0 + 2]) * dij[2]) / r;
-                vs = fmax(vs, ci + cj - fmin(proj, 0.0));
-            };
-            // canonical displacement x_R - x_L: the minimum image commutes with
-            // negation exactly, so both owners of the pair hold the same bits
-            const double sg = iL ? 1.0 : -1.0;
-            const T dT[3] = {(T)(sg * dij[0]), (T)(sg * dij[1]), (T)(sg * dij[2])};
-            PairOut<T> o = pair_flux<T, MFV, LIM>(ri, rj, iL, dT, (T)r, gam);
-            const double s = iL ? 1.0 : -1.0;
-            if (MFV) accm -= s * (double)o.Fm;
-            acc[0] -= s * (double)o.Fp[0];
-            acc[1] -= s * (double)o.Fp[1];
-            acc[2] -= s * (double)o.Fp[2];
-            acc[3] -= s * (double)o.FE;
-            nfall += o.fallback;
-            nclamp += o.clamp;
-            signal();
-            if (LEV) {
-                const double F[4] = {(double)o.Fp[0], (double)o.Fp[1], (double)o.Fp[2], (double)o.FE};
-                const int w = lj - bi;
-                if (w == 0) {   // both particles in one bin: most pairs
-#pragma unroll
-                    for (int c = 0; c < 4; c++) lacc[0][c] = lacc[0][c] - s * F[c];
-                } else if (w < kLevWin) {
-#pragma unroll
-                    for (int q = 1; q < kLevWin; q++)
-#pragma unroll
-                        for (int c = 0; c < 4; c++) lacc[q][c] = (q == w) ? lacc[q][c] - s * F[c] : lacc[q][c];
-                } else {
-                    for (int c = 0; c < 4; c++) lv.lev[((long long)lj * 4 + c) * n + li] -= s * F[c];
-                }
+                for (int c = 0; c < 4; c++) lv.lev[((long long)lc * 4 + c) * n + li] -= s * F[c];
             }
         }
+    }
+    if (act) {
         if (LEV) {
 #pragma unroll
             for (int w = 0; w < kLevWin; w++) {
@@ -1685,50 +1733,56 @@ __device__ __forceinline__ void fluxes_body(const PassArrays& a, const Phys& ph,
 }
 
 // One kernel per record precision: each pair holds both records in registers.
-// The FP32 form runs at four waves per SIMD.  The FP64 form runs at two: with
-// the list index loaded a pair ahead, a third wave (a few spilled loop
-// invariants, and twice the HBM traffic as more records compete for L2) no
-// longer pays.
+// The neighbours' records come by lane teams (team_load): per pair the FP64 form
+// made 16 loads of 64 cache lines each and the FP32 form 11, which the L1 takes
+// at about one line a clock and compute unit, the whole of the kernels' time on
+// even sets.  Now the arithmetic of the longest list of a wave bounds them.
+// Blocks of one wave: a block's LDS (16.3 KB FP64, 10.5 KB FP32) is free again
+// as soon as its wave ends.  The FP64 form runs at two waves per SIMD (its two
+// records alone are 128 VGPRs), the FP32 form at three.  Measured: FP64 MFM,
+// lattice 2.1M 1.84 -> 1.18 ms, clustered 16.8M 19.4 -> 15.7 ms; mixed MFM,
+// shock tube 295k 0.232 -> 0.181 ms; limited FP64, clustered 2.1M 4.35 -> 3.47
+// ms; levelled, hierarchical step of 2.1M 0.89 -> 0.69 ms a launch.
 constexpr int kFlux64Waves = 2;
 constexpr int kFluxMfvWaves = kFlux64Waves;
 template <bool LIM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kFlux64Waves))) void k_fluxes_f64(PassArrays a, Phys ph, const int* __restrict__ counts,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFlux64Waves))) void k_fluxes_f64(PassArrays a, Phys ph, const int* __restrict__ counts,
                                                     const int* __restrict__ list, const double* __restrict__ rec,
-                                                    Counters* cnt) {
-    fluxes_body<double, false, LIM>(a, ph, counts, list, rec, cnt);
+                                                    const double4* __restrict__ prim, Counters* cnt) {
+    fluxes_body<double, false, LIM>(a, ph, counts, list, rec, prim, cnt);
 }
 
 // The levelled pass of hierarchical steps (MFM, FP64 records).
 template <bool LIM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kFlux64Waves))) void k_fluxes_levels(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFlux64Waves))) void k_fluxes_levels(
     PassArrays a, Phys ph, const int* __restrict__ counts, const int* __restrict__ list,
-    const double* __restrict__ rec, Counters* cnt, Levels lv) {
-    fluxes_body<double, false, LIM, true>(a, ph, counts, list, rec, cnt, lv);
+    const double* __restrict__ rec, const double4* __restrict__ prim, Counters* cnt, Levels lv) {
+    fluxes_body<double, false, LIM, true>(a, ph, counts, list, rec, prim, cnt, lv);
 }
 
 // The finite-volume form, FP64 records only, at two waves per SIMD like the
 // FP64 form (at three its extra live values spill).
 template <bool LIM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kFluxMfvWaves))) void k_fluxes_mfv(PassArrays a, Phys ph, const int* __restrict__ counts,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFluxMfvWaves))) void k_fluxes_mfv(PassArrays a, Phys ph, const int* __restrict__ counts,
                                                     const int* __restrict__ list, const double* __restrict__ rec,
-                                                    Counters* cnt) {
-    fluxes_body<double, true, LIM>(a, ph, counts, list, rec, cnt);
+                                                    const double4* __restrict__ prim, Counters* cnt) {
+    fluxes_body<double, true, LIM>(a, ph, counts, list, rec, prim, cnt);
 }
 
-constexpr int kFlux32Waves = 4;
+constexpr int kFlux32Waves = 3;
 template <bool LIM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kFlux32Waves)))
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFlux32Waves)))
 void k_fluxes_f32(PassArrays a, Phys ph, const int* __restrict__ counts, const int* __restrict__ list,
-                  const float* __restrict__ rec, Counters* cnt) {
-    fluxes_body<float, false, LIM>(a, ph, counts, list, rec, cnt);
+                  const float* __restrict__ rec, const double4* __restrict__ prim, Counters* cnt) {
+    fluxes_body<float, false, LIM>(a, ph, counts, list, rec, prim, cnt);
 }
 
 // The finite-volume form on the FP32 records of the mixed form.
 template <bool LIM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kFlux32Waves)))
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFlux32Waves)))
 void k_fluxes_mfv_f32(PassArrays a, Phys ph, const int* __restrict__ counts, const int* __restrict__ list,
-                      const float* __restrict__ rec, Counters* cnt) {
-    fluxes_body<float, true, LIM>(a, ph, counts, list, rec, cnt);
+                      const float* __restrict__ rec, const double4* __restrict__ prim, Counters* cnt) {
+    fluxes_body<float, true, LIM>(a, ph, counts, list, rec, prim, cnt);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -1799,33 +1853,33 @@ void launch_gradients_active(const PassArrays& a, const Phys& ph, const unsigned
 
 template <bool LIM>
 static void launch_fluxes_lim(const PassArrays& a, const Phys& ph, const int* counts, const int* list, int mixed,
-                              int mfv, const void* rec, Counters* cnt, hipStream_t s) {
+                              int mfv, const void* rec, const double4* prim, Counters* cnt, hipStream_t s) {
     if (mfv && mixed)
-        k_fluxes_mfv_f32<LIM><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, counts, list, (const float*)rec, cnt);
+        k_fluxes_mfv_f32<LIM><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, counts, list, (const float*)rec, prim, cnt);
     else if (mfv)
-        k_fluxes_mfv<LIM><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, counts, list, (const double*)rec, cnt);
+        k_fluxes_mfv<LIM><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, counts, list, (const double*)rec, prim, cnt);
     else if (mixed)
-        k_fluxes_f32<LIM><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, counts, list, (const float*)rec, cnt);
+        k_fluxes_f32<LIM><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, counts, list, (const float*)rec, prim, cnt);
     else
-        k_fluxes_f64<LIM><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, counts, list, (const double*)rec, cnt);
+        k_fluxes_f64<LIM><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, counts, list, (const double*)rec, prim, cnt);
 }
 
 void launch_fluxes_levels(const PassArrays& a, const Phys& ph, const int* counts, const int* list, const void* rec,
-                          Counters* cnt, const long long* bin, int lmin, int nlev, double* lev,
+                          const double4* prim, Counters* cnt, const long long* bin, int lmin, int nlev, double* lev,
                           const long long* home, hipStream_t s) {
     const Levels lv{bin, lmin, nlev, lev, home};
     if (ph.limiter)
-        k_fluxes_levels<true><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, counts, list, (const double*)rec, cnt, lv);
+        k_fluxes_levels<true><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, counts, list, (const double*)rec, prim, cnt, lv);
     else
-        k_fluxes_levels<false><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, counts, list, (const double*)rec, cnt, lv);
+        k_fluxes_levels<false><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, counts, list, (const double*)rec, prim, cnt, lv);
 }
 
 void launch_fluxes(const PassArrays& a, const Phys& ph, const int* counts, const int* list, int mixed, int mfv,
-                   const void* rec, Counters* cnt, hipStream_t s) {
+                   const void* rec, const double4* prim, Counters* cnt, hipStream_t s) {
     if (ph.limiter)
-        launch_fluxes_lim<true>(a, ph, counts, list, mixed, mfv, rec, cnt, s);
+        launch_fluxes_lim<true>(a, ph, counts, list, mixed, mfv, rec, prim, cnt, s);
     else
-        launch_fluxes_lim<false>(a, ph, counts, list, mixed, mfv, rec, cnt, s);
+        launch_fluxes_lim<false>(a, ph, counts, list, mixed, mfv, rec, prim, cnt, s);
 }
 
 }  // namespace mfm

@@ -79,3 +79,29 @@ def test_lists_and_kernel_lengths_equal_brute_force(kind, n, n_ngb):
         assert torch.equal(got, want), (kind, a)
     print(f"{kind} {n}: residual of the neighbour-number equation {worst:.2e}", flush=True)
     assert worst <= TOL_COUNT
+
+
+@pytest.mark.parametrize("precision", [0, 1], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("n", [63, 64, 65, 193])
+def test_pass_at_the_edges_of_a_wave(n, precision):
+    """Sets that end just before, at and after a wave of 64 particles, in an open
+    box: every output against the oracle (the FP64 bar of the other pass tests,
+    the mixed bar for the mixed fluxes)."""
+    from oracle import oracle as O
+
+    from .gpu_util import compare_pass, run_pass
+    rng = np.random.default_rng(W.SEED_BASE + 760 + n)
+    w = W.Workload(name="edge", x=rng.uniform(0, 1, n), y=rng.uniform(0, 1, n), z=rng.uniform(0, 1, n),
+                   m=rng.uniform(0.5, 1.5, n) / n, vx=rng.normal(0, 0.2, n), vy=rng.normal(0, 0.2, n),
+                   vz=rng.normal(0, 0.2, n), u=rng.uniform(1, 2, n), gamma=1.4, box=(1.0, 1.0, 1.0),
+                   periodic=(0, 0, 0))
+    ref = O.hydro_pass(O.Setup.of(w), w.arrays())
+    ctx, st = run_pass(w, precision=precision)
+    ctx.check()
+    errs = compare_pass(st, ref)
+    print(n, precision, " ".join(f"{k}={v:.1e}" for k, v in errs.items()), flush=True)
+    for k, e in errs.items():
+        if precision == 0 or k in ("H", "nk", "V", "rho", "P"):
+            assert e <= 1e-12, (k, e)
+        elif k in ("dp", "dE"):
+            assert e <= 1e-5, (k, e)
