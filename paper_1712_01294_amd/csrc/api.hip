@@ -495,6 +495,9 @@ static mfm_status do_gradients(mfm_ctx* c, mfm_particles* p, hipStream_t s) {
         return fail(c, MFM_E_INVALID, "B, rho, P, grad, nk and V are required");
     if (!c->have_h || c->n_tree != p->n) return fail(c, MFM_E_STATE, "mfm_solve_h must run first");
     PassArrays a = arrays_of(p);
+    // counts holds the tail entries until the tails are sorted, the whole lists'
+    // lengths afterwards: a second gradient pass on one solve starts over
+    if (c->have_grad) launch_reset_tails((int)p->n, c->counts, s);
     c->rec_mixed = c->p.precision == MFM_MIXED;
     c->have_flux = 0;
     const auto ev = clock_take(c, MFM_KERNEL_GRADIENTS);
@@ -1115,9 +1118,7 @@ extern "C" mfm_status mfm_step_hier(mfm_ctx* c, mfm_particles* p, int64_t* bins,
         // step, whose last boundary passes over every particle), that pass's
         // kernel lengths, densities, volumes and gather lists still hold, and
         // only the gradients and the fluxes are evaluated again
-        if (chk.unmoved) {
-            launch_reset_counts((int)n, c->gcount, c->counts, s);
-        } else {
+        if (!chk.unmoved) {
             double* e1[1] = {(double*)b};
             if ((st = build(c, p, s, e1, 1))) return st;
             if ((st = do_solve_h(c, p, s))) return st;

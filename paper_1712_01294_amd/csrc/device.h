@@ -240,8 +240,8 @@ __device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xc07f);
 __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0f70); }
 
 // starts the loads of records j (one per lane, all 64 lanes); the earlier
-// records' reads must have returned
-template <int STRIDE, int C>
+// records' reads must have returned.  Chunks from USED on are left out.
+template <int STRIDE, int USED, int C>
 __device__ __forceinline__ void team_load(TeamLds<C>& S, const void* __restrict__ base, int j, int lane) {
     constexpr int kTeams = kWave / C;
     S.idx[(lane % kTeams) * C + lane / kTeams] = j;
@@ -254,10 +254,11 @@ __device__ __forceinline__ void team_load(TeamLds<C>& S, const void* __restrict_
     wait_lds();
 #pragma unroll
     for (int q = 0; q < C; q++) {
-        const int r = kTeams * q + team;
-        const char* g = (const char*)base + (size_t)(unsigned)js[q] * STRIDE + ((p - r) & (C - 1)) * 16;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
-                                         (__attribute__((address_space(3))) void*)(S.rec + q * kWave), 16, 0, 0);
+        const int r = kTeams * q + team, c = (p - r) & (C - 1);
+        const char* g = (const char*)base + (size_t)(unsigned)js[q] * STRIDE + c * 16;
+        if (USED == C || c < USED)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                             (__attribute__((address_space(3))) void*)(S.rec + q * kWave), 16, 0, 0);
     }
 }
 

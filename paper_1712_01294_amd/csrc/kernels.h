@@ -126,7 +126,7 @@ void launch_limit_bins(int n, int cap, const int* counts, const int* list, const
 // prim[4 i] (the packed neighbour record of the last gradient pass)
 void launch_same_positions(int n, const double* x, const double* y, const double* z, const double* H,
                            const double4* prim, unsigned long long* diff, hipStream_t s);
-void launch_reset_counts(int n, const int* gcount, int* counts, hipStream_t s);
+void launch_reset_tails(int n, int* counts, hipStream_t s);
 // the modes of one sub-step boundary: the cells (every level) of the due
 // particles are marked in marks (one bit per table entry, cleared here), and
 // a particle that is not due is kModeKept when the 3x3x3 cells around it, on

@@ -9,6 +9,8 @@
 #include <limits.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "device.h"
 #include "kernels.h"
 
@@ -437,7 +439,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kRootWaves)
         a.nk[i] = nk;
         a.V[i] = 1.0 / nk;
         gcount[i] = c;
-        counts[i] = c;
+        counts[i] = 0;   // tail entries, appended by the gradient kernel
     } else if (m > 0) {
         // not converged: the bracket goes on to the per-particle solver
         const unsigned long long slot = atomicAdd(fb_count, 1ull);
@@ -631,7 +633,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveSolveWa
             a.nk[i] = nk;
             a.V[i] = 1.0 / nk;
             gcount[i] = c;
-            counts[i] = c;
+            counts[i] = 0;
         }
         iters_max = max(iters_max, iters - iters0);
         scans_max = max(scans_max, (unsigned long long)scans);
@@ -753,7 +755,7 @@ __global__ __launch_bounds__(64) void k_solve_h_fallback(PassArrays a, TreeDesc 
             a.nk[i] = nk;
             a.V[i] = 1.0 / nk;
             gcount[i] = c;
-            counts[i] = c;
+            counts[i] = 0;
         }
         iters_max = max(iters_max, iters - iters0);
     }
@@ -811,7 +813,7 @@ __global__ __launch_bounds__(256) void k_gather_kept(PassArrays a, TreeDesc td, 
     }
     if (sel) {
         gcount[i] = min(c, cap);
-        counts[i] = c;   // beyond cap: an overflow, counted when the tails are sorted
+        counts[i] = max(c - cap, 0);   // beyond cap: an overflow, counted when the tails are sorted
     }
 }
 
@@ -843,10 +845,11 @@ __device__ __forceinline__ void bitonic_net(int* v) {
             }
 }
 
-// The tail of particle i (entries gcount[i] .. counts[i]-1 of its flux list,
-// appended by other particles in no fixed order: the first kTailNet in i's
+// The tail of particle i (counts[i] entries past the gcount[i] of its gather
+// part, appended by other particles in no fixed order: the first kTailNet in i's
 // contiguous tail buffer, the rest in the list) is sorted by index into the
-// list, so every later sum over the list runs in one order.  A short tail is
+// list, so every later sum over the list runs in one order; counts[i] becomes
+// the length of the whole list.  A short tail is
 // read from the buffer with vector loads, sorted in registers by a network
 // sized to the wave's longest tail, and written through per-lane LDS columns
 // a row at a time (the list is interleaved, list[k * n + i], and tails start
@@ -863,14 +866,14 @@ __global__ __launch_bounds__(256) void k_sort_tails(int n, int cap, const int* _
     if (i < n) {
         g = gcount[i];
         gsum = (unsigned long long)g;
-        int e = counts[i];
+        int e = g + counts[i];
         c = (unsigned long long)e;
         if (e > cap) {
             over = 1;
             flag_index(cnt, i);
             e = cap;
-            counts[i] = cap;
         }
+        counts[i] = e;
         t = e - g;
     }
     const bool net = t > 0 && t <= kTailNet;
@@ -953,22 +956,18 @@ __global__ __launch_bounds__(256) void k_sort_tails(int n, int cap, const int* _
 enum { R_X = 0, R_IH = 3, R_K = 4, R_RHO = 5, R_P = 6, R_V0 = 7, R_B = 10, R_G = 16, R_C = 31 };
 
 // What the gradient kernel reads of a neighbour, packed into one 128-byte line
-// per particle: (x, y, z, H), (rho, vx, vy, vz), (P, gather count, mode, -),
-// unused; the mode (hierarchical steps with active subsets) is 0 without one.
-__device__ __forceinline__ void pack_one(const PassArrays& a, const Phys& ph, const int* __restrict__ gcount,
-                                         const unsigned char* __restrict__ mode, double4* __restrict__ prim, int i) {
+// per particle: (x, y, z, H), (rho, vx, vy, vz), (P, -, -, -), unused.
+__device__ __forceinline__ void pack_one(const PassArrays& a, const Phys& ph, double4* __restrict__ prim, int i) {
     const double rho = a.m[i] * a.nk[i];
     prim[4 * (long long)i + 0] = make_double4(a.x[i], a.y[i], a.z[i], a.H[i]);
     prim[4 * (long long)i + 1] = make_double4(rho, a.vx[i], a.vy[i], a.vz[i]);
-    prim[4 * (long long)i + 2] = make_double4((ph.gamma - 1.0) * rho * a.u[i], (double)gcount[i],
-                                              mode ? (double)mode[i] : 0.0, 0.0);
+    prim[4 * (long long)i + 2] = make_double4((ph.gamma - 1.0) * rho * a.u[i], 0.0, 0.0, 0.0);
 }
 
-__global__ void k_pack_prim(PassArrays a, Phys ph, const int* __restrict__ gcount,
-                            const unsigned char* __restrict__ mode, double4* __restrict__ prim) {
+__global__ void k_pack_prim(PassArrays a, Phys ph, double4* __restrict__ prim) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= a.n) return;
-    pack_one(a, ph, gcount, mode, prim, i);
+    pack_one(a, ph, prim, i);
 }
 
 // A boundary with active subsets reads the records of the active particles'
@@ -983,38 +982,52 @@ __global__ void k_pack_prim_active(PassArrays a, Phys ph, const int* __restrict_
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= a.n || mode[i] != kModeSolve) return;
     const long long n = a.n;
-    pack_one(a, ph, gcount, mode, prim, i);
+    pack_one(a, ph, prim, i);
     const int cnum = gcount[i];
-    for (int k = 0; k < cnum; k++) pack_one(a, ph, gcount, mode, prim, list[(long long)k * n + i]);
+    for (int k = 0; k < cnum; k++) pack_one(a, ph, prim, list[(long long)k * n + i]);
 }
 
-// i is outside j's gather set: the pair enters j's flux list as a tail entry
-// (slots past the gather part, sorted afterwards); the first kTailNet go to
+// i is outside j's gather set: the pair enters j's flux list as its st-th tail
+// entry (past the gather part, sorted afterwards); the first kTailNet go to
 // j's contiguous tail buffer, so the appends to one particle share a cache
 // line, the rest to the list itself
-__device__ __forceinline__ void append_tail(int* __restrict__ counts, int* __restrict__ tails,
-                                            int* __restrict__ list, int cap, long long n, int j, int jgather, int i) {
-    const int slot = atomicAdd(&counts[j], 1);
-    const int st = slot - jgather;
+__device__ __forceinline__ void store_tail(int* __restrict__ tails, int* __restrict__ list,
+                                           const int* __restrict__ gcount, int cap, long long n, int j, int st, int i) {
     if (st < kTailNet) tails[(long long)j * kTailNet + st] = i;
-    else if (slot < cap) list[(long long)slot * n + j] = i;
+    else if (gcount[j] + st < cap) list[(long long)(gcount[j] + st) * n + j] = i;
 }
 
-// Four waves per SIMD (128 VGPRs, no spills): the kernel waits on the gathers
-// of its neighbours' records, and a fourth wave hides more of that than the
-// register budget it takes costs.
+// One thread per particle, one wave per block; the neighbours' records come by
+// lane teams, and while one is summed the next is on its way to LDS.  The tail
+// appends wait in LDS until the sums are done and then take their slots four
+// atomics at a time: each costs a round trip to L2, and in the loop a wave had
+// one in nearly every step.  The flux records leave through LDS too, in whole
+// 128-byte lines: 16-byte stores 256 bytes apart reached memory as partial
+// lines (14.7 GB written where records, outputs and tails hold 8.7 GB,
+// clustered 16.8M).  Three waves per SIMD: the sums, the record in hand and the
+// loop's values take 140 VGPRs, and a fourth wave spills.  Measured: lattice
+// 2.1M 1.06 -> 0.89 ms, shock tube 295k (mixed) 0.177 -> 0.124 ms; clustered
+// 16.8M stays at 13.9 ms, 5.7 of them for the appends.
 // With HIER (hierarchical steps with active subsets) only the particles of
 // mode kModeSolve get new gradients; a kept particle with a gather list only
 // appends itself to the lists of its active neighbours that do not reach it.
-constexpr int kGradWaves = 4;
+constexpr int kGradWaves = 3;
+constexpr int kAppends = 16;   // appends a lane holds back
+struct GradLds {
+    TeamLds<8> t;
+    int append[kAppends][kWave];
+};
 template <bool MIXED, bool HIER>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGradWaves))) void k_gradients(PassArrays a, Phys ph, const int* __restrict__ gcount,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))) void k_gradients(PassArrays a, Phys ph, const int* __restrict__ gcount,
                                                     int* __restrict__ counts, int* __restrict__ list, int* __restrict__ tails,
                                                     const double4* __restrict__ prim, void* __restrict__ recp,
                                                     Counters* cnt, const unsigned char* __restrict__ mode,
                                                     const long long* __restrict__ home) {
     cnt = counter_copy(cnt);
-    const int i = xcd_block() * 256 + threadIdx.x;
+    __shared__ GradLds lds;
+    TeamLds<8>& S8 = lds.t;
+    const int lane = threadIdx.x;
+    const int i = xcd_block() * kWave + lane;
     if (HIER && i < a.n && mode[i] == kModeKept) {
         const long long n = a.n;
         const double xi[3] = {a.x[i], a.y[i], a.z[i]};
@@ -1023,90 +1036,114 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGradWaves)
             const int j = list[(long long)k * n + i];
             if (mode[j] != kModeSolve) continue;   // the pair is not due (and j's record may be stale)
             const double4 pj = prim[4 * (long long)j + 0];
-            const double4 pg = prim[4 * (long long)j + 2];
             double d[3];
             displacement(ph, xi, pj.x, pj.y, pj.z, d);
             const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-            if (!(r < pj.w)) append_tail(counts, tails, list, ph.max_ngb, n, j, (int)pg.y, i);
+            if (!(r < pj.w)) store_tail(tails, list, gcount, ph.max_ngb, n, j, atomicAdd(&counts[j], 1), i);
         }
     }
     const bool act = i < a.n && (!HIER || mode[i] == kModeSolve);
     unsigned long long ill = 0, nonfin = 0, condbits = 0;
+    const long long n = a.n;
+    double xi[3] = {0.0, 0.0, 0.0}, phi_i[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    double Hi = 1.0, Vi = 1.0;
+    int cnum = 0;
     if (act) {
-        const long long n = a.n;
-        const double xi[3] = {a.x[i], a.y[i], a.z[i]};
-        const double Hi = a.H[i], Vi = a.V[i];
-        const double rho_i = a.m[i] * a.nk[i];
-        const double P_i = (ph.gamma - 1.0) * rho_i * a.u[i];
-        const double phi_i[5] = {rho_i, a.vx[i], a.vy[i], a.vz[i], P_i};
-        double E[6] = {0, 0, 0, 0, 0, 0};
-        double S[15];
-        double pmax[5], pmin[5];
+        xi[0] = a.x[i];
+        xi[1] = a.y[i];
+        xi[2] = a.z[i];
+        Hi = a.H[i];
+        Vi = a.V[i];
+        phi_i[0] = a.m[i] * a.nk[i];
+        phi_i[1] = a.vx[i];
+        phi_i[2] = a.vy[i];
+        phi_i[3] = a.vz[i];
+        phi_i[4] = (ph.gamma - 1.0) * phi_i[0] * a.u[i];
+        cnum = gcount[i];
+    }
+    const double rho_i = phi_i[0], P_i = phi_i[4];
+    double E[6] = {0, 0, 0, 0, 0, 0};
+    double S[15];
+    double pmax[5], pmin[5];
 #pragma unroll
-        for (int k = 0; k < 15; k++) S[k] = 0.0;
+    for (int k = 0; k < 15; k++) S[k] = 0.0;
 #pragma unroll
-        for (int f = 0; f < 5; f++) pmax[f] = pmin[f] = phi_i[f];
-        double rmax = 0.0;
-        const double norm = kernel_norm(Hi), iH = 1.0 / Hi;
-        const float normf = (float)norm, iHf = (float)iH;
-        const int cnum = gcount[i];
-        const int cap = ph.max_ngb;
-        // the next list entry is loaded one neighbour ahead, so the record
-        // loads do not wait for their index
-        int jn = cnum > 0 ? list[i] : 0;
-        for (int k = 0; k < cnum; k++) {
-            const int j = jn;
-            if (k + 1 < cnum) jn = list[(long long)(k + 1) * n + i];
-            const double4 pj = prim[4 * (long long)j + 0];
-            const double4 qj = prim[4 * (long long)j + 1];
-            const double2 pg = *(const double2*)&prim[4 * (long long)j + 2];
-            const double Pj = pg.x;
-            double d[3];
-            displacement(ph, xi, pj.x, pj.y, pj.z, d);
-            const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-            if (!(r < pj.w)) append_tail(counts, tails, list, cap, n, j, (int)pg.y, i);
-            const double phi_j[5] = {qj.x, qj.y, qj.z, qj.w, Pj};
-            if (!MIXED) {
-                const double psi = norm * spline_w(r * iH) * Vi;
-                E[0] += d[0] * d[0] * psi;
-                E[1] += d[0] * d[1] * psi;
-                E[2] += d[0] * d[2] * psi;
-                E[3] += d[1] * d[1] * psi;
-                E[4] += d[1] * d[2] * psi;
-                E[5] += d[2] * d[2] * psi;
+    for (int f = 0; f < 5; f++) pmax[f] = pmin[f] = phi_i[f];
+    double rmax = 0.0;
+    const double norm = kernel_norm(Hi), iH = 1.0 / Hi;
+    const float normf = (float)norm, iHf = (float)iH;
+    const int cap = ph.max_ngb;
+    const int self = i < a.n ? i : a.n - 1;   // a record to load where a lane has no neighbour
+    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i(cnum));
+    auto entry = [&](int k) { return k < cnum ? list[(long long)k * n + i] : -1; };
+    int j = entry(0), jn = entry(1);
+    int napp = 0;
+    if (kmax > 0) team_load<128, 5>(S8, prim, j >= 0 ? j : self, lane);
+    for (int k = 0; k < kmax; k++) {
+        wait_vmem();
+        wave_lds_sync();
+        double rec[10];   // x, y, z, H, rho, vx, vy, vz, P
 #pragma unroll
-                for (int f = 0; f < 5; f++) {
-                    const double df = (phi_j[f] - phi_i[f]) * psi;
-                    S[3 * f + 0] += df * d[0];
-                    S[3 * f + 1] += df * d[1];
-                    S[3 * f + 2] += df * d[2];
-                }
-            } else {
-                // the pairwise kernel weight in FP32; the moments and sums in FP64, so
-                // that E and the gradient sums share one set of weights and the
-                // conditioning of E does not amplify per-product rounding
-                const double psi = (double)(normf * spline_w((float)r * iHf)) * Vi;
-                E[0] += d[0] * d[0] * psi;
-                E[1] += d[0] * d[1] * psi;
-                E[2] += d[0] * d[2] * psi;
-                E[3] += d[1] * d[1] * psi;
-                E[4] += d[1] * d[2] * psi;
-                E[5] += d[2] * d[2] * psi;
-#pragma unroll
-                for (int f = 0; f < 5; f++) {
-                    const double df = (phi_j[f] - phi_i[f]) * psi;
-                    S[3 * f + 0] += df * d[0];
-                    S[3 * f + 1] += df * d[1];
-                    S[3 * f + 2] += df * d[2];
-                }
-            }
-#pragma unroll
-            for (int f = 0; f < 5; f++) {
-                pmax[f] = fmax(pmax[f], phi_j[f]);
-                pmin[f] = fmin(pmin[f], phi_j[f]);
-            }
-            rmax = fmax(rmax, r);
+        for (int c = 0; c < 5; c++) {
+            const uint4 u = team_chunk(S8, c, lane);
+            __builtin_memcpy(rec + 2 * c, &u, 16);
         }
+        const int jc = j;
+        j = jn;
+        wave_lds_sync();
+        wait_lds();
+        if (k + 1 < kmax) team_load<128, 5>(S8, prim, j >= 0 ? j : self, lane);
+        jn = entry(k + 2);
+        if (jc < 0) continue;
+        double d[3];
+        displacement(ph, xi, rec[0], rec[1], rec[2], d);
+        const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+        if (!(r < rec[3])) {
+            if (napp < kAppends) lds.append[napp][lane] = jc;
+            else store_tail(tails, list, gcount, cap, n, jc, atomicAdd(&counts[jc], 1), i);
+            napp++;
+        }
+        const double* phi_j = rec + 4;
+        // MIXED: the pairwise kernel weight in FP32; the moments and sums in FP64, so
+        // that E and the gradient sums share one set of weights and the
+        // conditioning of E does not amplify per-product rounding
+        const double psi = MIXED ? (double)(normf * spline_w((float)r * iHf)) * Vi : norm * spline_w(r * iH) * Vi;
+        E[0] += d[0] * d[0] * psi;
+        E[1] += d[0] * d[1] * psi;
+        E[2] += d[0] * d[2] * psi;
+        E[3] += d[1] * d[1] * psi;
+        E[4] += d[1] * d[2] * psi;
+        E[5] += d[2] * d[2] * psi;
+#pragma unroll
+        for (int f = 0; f < 5; f++) {
+            const double df = (phi_j[f] - phi_i[f]) * psi;
+            S[3 * f + 0] += df * d[0];
+            S[3 * f + 1] += df * d[1];
+            S[3 * f + 2] += df * d[2];
+        }
+#pragma unroll
+        for (int f = 0; f < 5; f++) {
+            pmax[f] = fmax(pmax[f], phi_j[f]);
+            pmin[f] = fmin(pmin[f], phi_j[f]);
+        }
+        rmax = fmax(rmax, r);
+    }
+    {
+        const int held = min(napp, kAppends);
+        const int most = __builtin_amdgcn_readfirstlane(wave_max_i(held));
+        for (int b = 0; b < most; b += 4) {
+            int to[4], st[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++) to[q] = b + q < held ? lds.append[b + q][lane] : -1;
+#pragma unroll
+            for (int q = 0; q < 4; q++) st[q] = to[q] >= 0 ? atomicAdd(&counts[to[q]], 1) : 0;
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                if (to[q] >= 0) store_tail(tails, list, gcount, cap, n, to[q], st[q], i);
+        }
+    }
+    // (lanes without a particle run along on zeros and store nothing)
+    {
         // B = E^-1 by cofactors (E symmetric: xx xy xz yy yz zz)
         const double c00 = E[3] * E[5] - E[4] * E[4];
         const double c01 = E[2] * E[4] - E[1] * E[5];
@@ -1120,11 +1157,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGradWaves)
         const double fe = E[0] * E[0] + E[3] * E[3] + E[5] * E[5] + 2.0 * (E[1] * E[1] + E[2] * E[2] + E[4] * E[4]);
         const double fb = B[0] * B[0] + B[3] * B[3] + B[5] * B[5] + 2.0 * (B[1] * B[1] + B[2] * B[2] + B[4] * B[4]);
         const double cond = sqrt(fe) * sqrt(fb);
-        if (!(det > 0.0) || !(cond <= ph.cond_max)) {
+        if (act && (!(det > 0.0) || !(cond <= ph.cond_max))) {
             ill = 1;
             flag_index(cnt, i);
         }
-        if (cond > 0.0) condbits = __double_as_longlong(cond);
+        if (act && cond > 0.0) condbits = __double_as_longlong(cond);
         // the limiter constant: beta, or with the optional limiters (R24) beta moved
         // towards beta_min linearly in log10(cond) between cond_lo and cond_hi
         double beta = ph.beta;
@@ -1170,66 +1207,70 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGradWaves)
             g[3 * f + 1] = alpha * g1;
             g[3 * f + 2] = alpha * g2;
         }
-        const long long io = HIER ? home[i] : i;   // column of B, grad and alpha
+        if (act) {
+            const long long io = HIER ? home[i] : i;   // column of B, grad and alpha
 #pragma unroll
-        for (int k = 0; k < 6; k++) a.B[k * n + io] = B[k];
+            for (int k = 0; k < 6; k++) a.B[k * n + io] = B[k];
 #pragma unroll
-        for (int k = 0; k < 15; k++) {
-            a.grad[k * n + io] = g[k];
-            if (!isfinite(g[k])) nonfin = 1;
+            for (int k = 0; k < 15; k++) {
+                a.grad[k * n + io] = g[k];
+                if (!isfinite(g[k])) nonfin = 1;
+            }
+            if (a.alpha) {
+#pragma unroll
+                for (int f = 0; f < 5; f++) a.alpha[f * n + io] = al[f];
+            }
+            a.rho[i] = rho_i;
+            a.P[i] = P_i;
         }
-        if (a.alpha) {
-#pragma unroll
-            for (int f = 0; f < 5; f++) a.alpha[f * n + io] = al[f];
-        }
-        a.rho[i] = rho_i;
-        a.P[i] = P_i;
         const double c_i = sqrt(ph.gamma * P_i / rho_i);
-        if (!MIXED) {
-            double* rec = (double*)recp + (long long)i * 32;
-            double v[32];
+        using T = typename std::conditional<MIXED, float, double>::type;
+        T v[32];
+        if constexpr (!MIXED) {
             v[0] = xi[0];
             v[1] = xi[1];
             v[2] = xi[2];
-            v[R_IH] = iH;
-            v[R_K] = Vi * Vi * norm;
-            v[R_RHO] = rho_i;
-            v[R_P] = P_i;
-            v[R_V0 + 0] = phi_i[1];
-            v[R_V0 + 1] = phi_i[2];
-            v[R_V0 + 2] = phi_i[3];
-#pragma unroll
-            for (int k = 0; k < 6; k++) v[R_B + k] = B[k];
-#pragma unroll
-            for (int k = 0; k < 15; k++) v[R_G + k] = g[k];
-            v[R_C] = c_i;
-            double2* r2 = (double2*)rec;
-#pragma unroll
-            for (int k = 0; k < 16; k++) r2[k] = make_double2(v[2 * k], v[2 * k + 1]);
         } else {
-            float* rec = (float*)recp + (long long)i * 32;
-            float v[32];
             // slots 0-1: the pressure in FP64 (its two halves), for the pressure
             // difference across a face; slot 2 unused
             const long long pbits = __double_as_longlong(P_i);
             v[0] = __int_as_float((int)(pbits & 0xffffffffll));
             v[1] = __int_as_float((int)(pbits >> 32));
             v[2] = 0.0f;
-            v[R_IH] = (float)iH;
-            v[R_K] = (float)(Vi * Vi * norm);
-            v[R_RHO] = (float)rho_i;
-            v[R_P] = (float)P_i;
-            v[R_V0 + 0] = (float)phi_i[1];
-            v[R_V0 + 1] = (float)phi_i[2];
-            v[R_V0 + 2] = (float)phi_i[3];
+        }
+        v[R_IH] = (T)iH;
+        v[R_K] = (T)(Vi * Vi * norm);
+        v[R_RHO] = (T)rho_i;
+        v[R_P] = (T)P_i;
 #pragma unroll
-            for (int k = 0; k < 6; k++) v[R_B + k] = (float)B[k];
+        for (int c = 0; c < 3; c++) v[R_V0 + c] = (T)phi_i[1 + c];
 #pragma unroll
-            for (int k = 0; k < 15; k++) v[R_G + k] = (float)g[k];
-            v[R_C] = (float)c_i;
-            float4* r4 = (float4*)rec;
+        for (int k = 0; k < 6; k++) v[R_B + k] = (T)B[k];
 #pragma unroll
-            for (int k = 0; k < 8; k++) r4[k] = make_float4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+        for (int k = 0; k < 15; k++) v[R_G + k] = (T)g[k];
+        v[R_C] = (T)c_i;
+        // the wave's records, 128 bytes of each at a time, transposed in LDS: eight
+        // lanes then store one record's line
+        const unsigned long long stored = __ballot(act);
+        const int r0 = i - lane, team = lane / 8;
+#pragma unroll
+        for (int h = 0; h < (int)sizeof(T) / 4; h++) {
+            wave_lds_sync();
+#pragma unroll
+            for (int c = 0; c < 8; c++) {
+                uint4 u;
+                __builtin_memcpy(&u, v + (8 * h + c) * (16 / sizeof(T)), 16);
+                S8.rec[lane * 8 + ((c + lane) & 7)] = u;
+            }
+            wave_lds_sync();
+            const int c = (lane - team) & 7;   // the chunk at this lane's slots
+#pragma unroll
+            for (int q = 0; q < 8; q++) {
+                const int r = 8 * q + team;
+                const uint4 u = S8.rec[q * kWave + lane];
+                if ((stored >> r) & 1)
+                    *(uint4*)((char*)recp + (size_t)(unsigned)(r0 + r) * (32 * sizeof(T)) + 128 * h + 16 * c) = u;
+            }
         }
     }
     count_add(&cnt->illcond, ill);
@@ -1626,8 +1667,8 @@ __device__ __forceinline__ void fluxes_body(const PassArrays& a, const Phys& ph,
     auto start = [&](bool on, int j) {
         if (LEV && !__ballot(on)) return;
         const int jr = on ? j : self;
-        team_load<32 * sizeof(T)>(S.rec, rec, jr, lane);
-        if constexpr (sizeof(T) == 4) team_load<128>(S.pos, prim, jr, lane);
+        team_load<32 * sizeof(T), 2 * sizeof(T)>(S.rec, rec, jr, lane);
+        if constexpr (sizeof(T) == 4) team_load<128, 2>(S.pos, prim, jr, lane);
     };
     int j = entry(0), jn = entry(1);
     int lj = LEV ? level(j) : 0;
@@ -1812,13 +1853,13 @@ void launch_solve_h(const PassArrays& a, const TreeDesc& td, const int2* tab,
 void launch_gradients(const PassArrays& a, const Phys& ph, const int* gcount, int* counts, int* list, int* tails,
                       int mixed, double4* prim, void* rec, Counters* cnt, hipEvent_t t0, hipEvent_t t1,
                       hipStream_t s) {
-    k_pack_prim<<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, gcount, nullptr, prim);
+    k_pack_prim<<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, prim);
     if (t0) hipEventRecord(t0, s);
     if (mixed)
-        k_gradients<true, false><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, gcount, counts, list, tails, prim, rec,
+        k_gradients<true, false><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, gcount, counts, list, tails, prim, rec,
                                                                      cnt, nullptr, nullptr);
     else
-        k_gradients<false, false><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, gcount, counts, list, tails, prim, rec,
+        k_gradients<false, false><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, gcount, counts, list, tails, prim, rec,
                                                                       cnt, nullptr, nullptr);
     if (t1) hipEventRecord(t1, s);
     k_sort_tails<<<blocks_of(a.n, 256), 256, 0, s>>>(a.n, ph.max_ngb, gcount, counts, list, tails, cnt);
@@ -1845,10 +1886,10 @@ void launch_gradients_active(const PassArrays& a, const Phys& ph, const unsigned
                              const int* gcount, int* counts, int* list, int* tails, double4* prim, void* rec,
                              Counters* cnt, hipStream_t s) {
     k_pack_prim_active<<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, gcount, mode, list, prim);
-    k_gradients<false, true><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, gcount, counts, list, tails, prim, rec, cnt,
+    k_gradients<false, true><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, gcount, counts, list, tails, prim, rec, cnt,
                                                                  mode, home);
-    k_pack_rec_kept<<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, mode, home, counts, (double*)rec);
     k_sort_tails<<<blocks_of(a.n, 256), 256, 0, s>>>(a.n, ph.max_ngb, gcount, counts, list, tails, cnt);
+    k_pack_rec_kept<<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, mode, home, counts, (double*)rec);
 }
 
 template <bool LIM>

@@ -425,16 +425,14 @@ void launch_limit_bins(int n, int cap, const int* counts, const int* list, const
     k_limit_bins<<<(n + 255) / 256, 256, 0, s>>>(n, cap, counts, list, bin, out, raised);
 }
 
-// the flux lists back to their gather parts (counts = gcount), for a gradient
+// the flux lists back to their gather parts (no tail entries), for a gradient
 // pass that appends the tails again over the lists of an earlier solve
-__global__ void k_reset_counts(int n, const int* __restrict__ gcount, int* __restrict__ counts) {
+__global__ void k_reset_tails(int n, int* __restrict__ counts) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) counts[i] = gcount[i];
+    if (i < n) counts[i] = 0;
 }
 
-void launch_reset_counts(int n, const int* gcount, int* counts, hipStream_t s) {
-    k_reset_counts<<<(n + 255) / 256, 256, 0, s>>>(n, gcount, counts);
-}
+void launch_reset_tails(int n, int* counts, hipStream_t s) { k_reset_tails<<<(n + 255) / 256, 256, 0, s>>>(n, counts); }
 
 // ------------------------------------------- active subsets of hierarchical steps
 // x wrapped into the box on periodic axes (positions between builds of a
