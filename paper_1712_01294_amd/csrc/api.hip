@@ -41,7 +41,8 @@ struct mfm_ctx {
     int *counts = nullptr, *gcount = nullptr, *list = nullptr;
     int* fb_list = nullptr;               // particles handed to the per-particle kernel-length solve
     unsigned long long* fb_count = nullptr;
-    int* tails = nullptr;                 // per-particle tail buffers of the flux lists (kTailBuf slots)
+    int2* bin_entry = nullptr;            // tail entries of the flux lists, in bins of 256 particles
+    int* bin_fill = nullptr;              // entries per bin
     int* fb2_list = nullptr;              // particles the list solver hands to the rescanning one
     unsigned long long* fb2_count = nullptr;
     void* rec = nullptr;                  // 32 x 8 B per particle
@@ -244,7 +245,7 @@ void mfm_destroy(mfm_ctx* c) {
         }
     }
     void* bufs[] = {c->keys, c->ktmp, c->idx, c->vtmp, c->hist, c->scan_tmp, c->gtmp, c->tab, c->pos, c->rl,
-                    c->counts, c->gcount, c->list, c->fb_list, c->fb_count, c->fb2_list, c->fb2_count, c->tails, c->rec, c->prim, c->vp, c->up, c->Ehalf, c->mp, c->dt_part, c->dt_out, c->cnt, c->adj, c->lev,
+                    c->counts, c->gcount, c->list, c->fb_list, c->fb_count, c->fb2_list, c->fb2_count, c->bin_entry, c->bin_fill, c->rec, c->prim, c->vp, c->up, c->Ehalf, c->mp, c->dt_part, c->dt_out, c->cnt, c->adj, c->lev,
                     c->hmode, c->hmarks, c->hhome, c->hmoved};
     for (void* b : bufs)
         if (b) hipFree(b);
@@ -284,7 +285,8 @@ mfm_status mfm_create(const mfm_params* params, int64_t capacity, mfm_ctx** out)
     alloc((void**)&c->fb_list, sizeof(int) * n, "fallback list");
     alloc((void**)&c->fb_count, sizeof(unsigned long long), "fallback count");
     alloc((void**)&c->fb2_list, sizeof(int) * n, "second fallback list");
-    alloc((void**)&c->tails, sizeof(int) * (size_t)kTailBuf * n, "tail buffers");
+    alloc((void**)&c->bin_entry, sizeof(int2) * (size_t)kBinEntries * n, "tail bins");
+    alloc((void**)&c->bin_fill, sizeof(int) * ((n + 255) / 256), "tail bin counts");
     alloc((void**)&c->fb2_count, sizeof(unsigned long long), "second fallback count");
     alloc((void**)&c->rec, sizeof(double) * 32 * n, "records");
     alloc((void**)&c->prim, sizeof(double4) * 4 * n, "neighbour records");
@@ -495,13 +497,13 @@ static mfm_status do_gradients(mfm_ctx* c, mfm_particles* p, hipStream_t s) {
         return fail(c, MFM_E_INVALID, "B, rho, P, grad, nk and V are required");
     if (!c->have_h || c->n_tree != p->n) return fail(c, MFM_E_STATE, "mfm_solve_h must run first");
     PassArrays a = arrays_of(p);
-    // counts holds the tail entries until the tails are sorted, the whole lists'
-    // lengths afterwards: a second gradient pass on one solve starts over
+    // counts holds the tail entries past the bins until the tails are sorted, the
+    // whole lists' lengths afterwards: a second gradient pass on one solve starts over
     if (c->have_grad) launch_reset_tails((int)p->n, c->counts, s);
     c->rec_mixed = c->p.precision == MFM_MIXED;
     c->have_flux = 0;
     const auto ev = clock_take(c, MFM_KERNEL_GRADIENTS);
-    launch_gradients(a, c->ph, c->gcount, c->counts, c->list, c->tails, c->rec_mixed, c->prim, c->rec, c->cnt, ev.first,
+    launch_gradients(a, c->ph, c->gcount, c->counts, c->list, c->bin_entry, c->bin_fill, c->rec_mixed, c->prim, c->rec, c->cnt, ev.first,
                      ev.second, s);
     c->have_grad = 1;
     c->last = s;
@@ -1040,7 +1042,7 @@ static mfm_status do_pass_active(mfm_ctx* c, mfm_particles* q, const long long* 
                       c->gcount, c->counts, s);
     launch_solve_h_active(a, c->td, c->tab, c->pos, c->keys, c->ph, c->cnt, c->hmode, c->hmoved + n, c->rl, c->list,
                           c->gcount, c->counts, c->fb_list, c->fb_count, c->fb2_list, c->fb2_count, s);
-    launch_gradients_active(a, c->ph, c->hmode, c->hhome, c->gcount, c->counts, c->list, c->tails, c->prim, c->rec,
+    launch_gradients_active(a, c->ph, c->hmode, c->hhome, c->gcount, c->counts, c->list, c->bin_entry, c->bin_fill, c->prim, c->rec,
                             c->cnt, s);
     c->have_h = c->have_grad = 1;
     c->rec_mixed = 0;
@@ -1291,7 +1293,8 @@ constexpr size_t kNoAllocSizes[] = {
     8,                                        // fb_count
     4 * N_,                                   // fb2_list
     8,                                        // fb2_count
-    4 * (size_t)kTailBuf * N_,                // tails
+    8 * (size_t)kBinEntries * N_,             // bin_entry
+    4 * (N_ / 256),                           // bin_fill
     8 * 32 * N_,                              // rec
     32 * 4 * N_,                              // prim
     (size_t)kCounterCopies * kCounterStride,  // cnt
@@ -1315,7 +1318,8 @@ void noalloc_carve(mfm_ctx* c, unsigned char* base) {
     void** dst[] = {(void**)&c->keys, (void**)&c->ktmp, (void**)&c->idx, (void**)&c->vtmp, (void**)&c->hist,
                     (void**)&c->scan_tmp, (void**)&c->gtmp, (void**)&c->tab, (void**)&c->pos, (void**)&c->rl,
                     (void**)&c->counts, (void**)&c->gcount, (void**)&c->list, (void**)&c->fb_list,
-                    (void**)&c->fb_count, (void**)&c->fb2_list, (void**)&c->fb2_count, (void**)&c->tails,
+                    (void**)&c->fb_count, (void**)&c->fb2_list, (void**)&c->fb2_count, (void**)&c->bin_entry,
+                    (void**)&c->bin_fill,
                     (void**)&c->rec, (void**)&c->prim, (void**)&c->cnt};
     static_assert(sizeof(dst) / sizeof(dst[0]) == sizeof(kNoAllocSizes) / sizeof(kNoAllocSizes[0]),
                   "one size per carved buffer");

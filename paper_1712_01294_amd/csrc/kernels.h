@@ -51,9 +51,9 @@ void launch_solve_h(const PassArrays& a, const TreeDesc& td, const int2* tab,
                     int* list, int* gcount,
                     int* counts, int* fb_list, unsigned long long* fb_count, int* fb2_list,
                     unsigned long long* fb2_count, hipEvent_t t0, hipEvent_t t1, hipStream_t s);
-// flux-list tail entries per particle held in its contiguous tail buffer
-constexpr int kTailBuf = 32;
-void launch_gradients(const PassArrays& a, const Phys& ph, const int* gcount, int* counts, int* list, int* tails,
+// flux-list tail entries kept per particle, in bins of 256 particles
+constexpr int kBinEntries = 16;
+void launch_gradients(const PassArrays& a, const Phys& ph, const int* gcount, int* counts, int* list, int2* bin_entry, int* bin_fill,
                       int mixed, double4* prim, void* rec, Counters* cnt, hipEvent_t t0, hipEvent_t t1,
                       hipStream_t s);
 void launch_fluxes(const PassArrays& a, const Phys& ph, const int* counts, const int* list,
@@ -82,7 +82,7 @@ void launch_solve_h_active(const PassArrays& a, const TreeDesc& td, const int2* 
 // (the new gradient matrices and limited gradients of the active particles, and
 // the kept ones read for the records, at column home[i] of B and grad)
 void launch_gradients_active(const PassArrays& a, const Phys& ph, const unsigned char* mode, const long long* home,
-                             const int* gcount, int* counts, int* list, int* tails, double4* prim, void* rec,
+                             const int* gcount, int* counts, int* list, int2* bin_entry, int* bin_fill, double4* prim, void* rec,
                              Counters* cnt, hipStream_t s);
 // step.hip
 void launch_kick_drift(const PassArrays& a, const Phys& ph, double dt, double u_floor,

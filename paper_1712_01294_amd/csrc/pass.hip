@@ -823,8 +823,35 @@ __global__ __launch_bounds__(256) void k_gather_kept(PassArrays a, TreeDesc td, 
 // gather list anyway, appends each such j to i's list (atomic slot); then each
 // list sorts its appended tail by index so the list, and every sum over it, is
 // deterministic.
-constexpr int kTailNet = kTailBuf;   // tails up to this length are buffered and sorted in registers
-static_assert(kTailNet % 4 == 0, "tail buffers are read as int4");
+constexpr int kTailNet = 32;   // tails up to this length are sorted in registers
+
+// Tail entries travel in bins, one per 256 consecutive particles: an entry is
+// (i, j mod 256), appended to j's bin by whoever met the pair.  A wave's
+// appends go to a few bins, so it takes one atomic per bin and writes runs of
+// entries, where an atomic and a 4-byte store per entry, each to a line of its
+// own, cost the gradient kernel 5.7 of its 14 ms (clustered 16.8M).  What a bin
+// cannot hold is counted per particle in counts and put at the end of the
+// particle's list slots, from the last one down.
+struct Bins {
+    int2* entry;    // kBinEntries per particle
+    int* fill;      // entries per bin (appended ones, which may exceed what it holds)
+};
+__device__ __forceinline__ int bin_room(int bin, int n) { return kBinEntries * min(256, n - (bin << 8)); }
+__device__ __forceinline__ void bin_store(const Bins& bins, int* __restrict__ counts, int* __restrict__ list,
+                                          const int* __restrict__ gcount, int cap, int n, int j, int at, int i) {
+    const int bin = j >> 8;
+    if (at < bin_room(bin, n)) {
+        bins.entry[(long long)bin * (256 * kBinEntries) + at] = make_int2(i, j & 255);
+    } else {
+        const int s = atomicAdd(&counts[j], 1);
+        if (gcount[j] + s < cap) list[(long long)(cap - 1 - s) * n + j] = i;
+    }
+}
+// one append by the calling lane alone
+__device__ __forceinline__ void bin_append(const Bins& bins, int* __restrict__ counts, int* __restrict__ list,
+                                           const int* __restrict__ gcount, int cap, int n, int j, int i) {
+    bin_store(bins, counts, list, gcount, cap, n, j, atomicAdd(&bins.fill[j >> 8], 1), i);
+}
 
 // bitonic sorting network on N registers (indices fixed at compile time)
 template <int N>
@@ -845,28 +872,45 @@ __device__ __forceinline__ void bitonic_net(int* v) {
             }
 }
 
-// The tail of particle i (counts[i] entries past the gcount[i] of its gather
-// part, appended by other particles in no fixed order: the first kTailNet in i's
-// contiguous tail buffer, the rest in the list) is sorted by index into the
-// list, so every later sum over the list runs in one order; counts[i] becomes
-// the length of the whole list.  A short tail is
-// read from the buffer with vector loads, sorted in registers by a network
-// sized to the wave's longest tail, and written through per-lane LDS columns
-// a row at a time (the list is interleaved, list[k * n + i], and tails start
-// at different rows), each store one coalesced row segment of the wave's
-// columns.  Longer tails are ranked by the whole wave in LDS.
+// The tails of a block's 256 particles, from their bin: the entries are dealt to
+// their particles in LDS, sorted by index and written behind the gather parts,
+// so every later sum over a list runs in one order; counts[i] becomes the length
+// of the whole list.  A short tail is sorted in registers by a network sized to
+// the wave's longest such tail, and written through its LDS column a row at a
+// time (the list is interleaved, list[k * n + i], and tails start at different
+// rows), each store one coalesced row segment of the wave's columns.  Longer
+// tails, and those with entries that the bin could not hold, are ranked by the
+// whole wave in LDS.
 __global__ __launch_bounds__(256) void k_sort_tails(int n, int cap, const int* __restrict__ gcount,
-                                                     int* __restrict__ counts, int* __restrict__ list,
-                                                     const int* __restrict__ tails, Counters* cnt) {
+                                                     int* __restrict__ counts, int* __restrict__ list, Bins bins,
+                                                     Counters* cnt) {
     cnt = counter_copy(cnt);
     __shared__ int col[kTailNet][256];
-    const int i = xcd_block() * 256 + threadIdx.x;
+    __shared__ int dealt[256], gathered[256];
+    const int bin = xcd_block();
+    const int i = bin * 256 + threadIdx.x;
     unsigned long long c = 0, over = 0, gsum = 0;
-    int g = 0, t = 0;
+    int g = 0, t = 0, extra = 0;
     if (i < n) {
         g = gcount[i];
+        extra = counts[i];
+    }
+    dealt[threadIdx.x] = 0;
+    gathered[threadIdx.x] = g;
+    __syncthreads();
+    const int fill = min(bins.fill[bin], bin_room(bin, n));
+    const int2* __restrict__ entry = bins.entry + (long long)bin * (256 * kBinEntries);
+    for (int e = threadIdx.x; e < fill; e += 256) {
+        const int2 x = entry[e];
+        const int s = atomicAdd(&dealt[x.y], 1);
+        if (s < kTailNet) col[s][x.y] = x.x;
+        else if (gathered[x.y] + s < cap) list[(long long)(gathered[x.y] + s) * n + bin * 256 + x.y] = x.x;
+    }
+    __syncthreads();
+    const int from_bin = dealt[threadIdx.x];
+    if (i < n) {
         gsum = (unsigned long long)g;
-        int e = g + counts[i];
+        int e = g + from_bin + extra;
         c = (unsigned long long)e;
         if (e > cap) {
             over = 1;
@@ -876,23 +920,12 @@ __global__ __launch_bounds__(256) void k_sort_tails(int n, int cap, const int* _
         counts[i] = e;
         t = e - g;
     }
-    const bool net = t > 0 && t <= kTailNet;
+    const bool net = t > 0 && t <= kTailNet && extra == 0;
     const int tmax = wave_max_i(net ? t : 0);
     if (tmax > 0) {
         int v[kTailNet];
-        if (net) {
-            const int4* tb = (const int4*)(tails + (long long)i * kTailNet);
 #pragma unroll
-            for (int q = 0; q < kTailNet / 4; q++) {
-                const int4 x = tb[q];
-                v[4 * q] = x.x;
-                v[4 * q + 1] = x.y;
-                v[4 * q + 2] = x.z;
-                v[4 * q + 3] = x.w;
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kTailNet; k++) v[k] = net && k < t ? v[k] : INT_MAX;
+        for (int k = 0; k < kTailNet; k++) v[k] = net && k < t ? col[k][threadIdx.x] : INT_MAX;
         if (tmax <= 8) bitonic_net<8>(v);
         else if (tmax <= 16) bitonic_net<16>(v);
         else bitonic_net<kTailNet>(v);
@@ -904,19 +937,26 @@ __global__ __launch_bounds__(256) void k_sort_tails(int n, int cap, const int* _
         for (int r = rlo; r < rhi; r++)
             if (net && r >= g && r < g + t) list[(long long)r * n + i] = col[r - g][threadIdx.x];
     }
+    if (t > 0 && !net) {
+        // the whole tail into its slots: what was dealt to the column, and the
+        // entries at the end of the particle's slots (moved down in order)
+        for (int k = 0; k < min(kTailNet, min(from_bin, t)); k++) list[(long long)(g + k) * n + i] = col[k][threadIdx.x];
+        const int kept = min(extra, cap - g);
+        for (int k = 0; k < kept && from_bin + k < t; k++)
+            list[(long long)(g + from_bin + k) * n + i] = list[(long long)(cap - kept + k) * n + i];
+    }
     // Long tails, one at a time per wave: the tail goes to a contiguous LDS
     // region of the wave, every lane ranks its entries against all of them (ties,
     // which a list does not hold, by position) and writes each entry to its slot.
-    __syncthreads();   // every wave is done with the columns
+    __syncthreads();   // every wave is done with the columns, and the moves above are visible
     int* wb = &col[0][0] + (threadIdx.x >> 6) * (kTailNet * kWave);
     const int lane = threadIdx.x & (kWave - 1);
-    unsigned long long lm = __ballot(t > kTailNet && t <= kTailNet * kWave);
+    unsigned long long lm = __ballot(t > 0 && !net && t <= kTailNet * kWave);
     while (lm) {
         const int src = __ffsll((long long)lm) - 1;
         lm &= lm - 1;
         const int gs = __shfl(g, src, kWave), ts = __shfl(t, src, kWave), is = __shfl(i, src, kWave);
-        for (int k = lane; k < ts; k += kWave)
-            wb[k] = k < kTailNet ? tails[(long long)is * kTailNet + k] : list[(long long)(gs + k) * n + is];
+        for (int k = lane; k < ts; k += kWave) wb[k] = list[(long long)(gs + k) * n + is];
         wave_lds_sync();
         for (int k = lane; k < ts; k += kWave) {
             const int v = wb[k];
@@ -930,8 +970,7 @@ __global__ __launch_bounds__(256) void k_sort_tails(int n, int cap, const int* _
         wave_lds_sync();   // the next tail overwrites the region
     }
     if (t > kTailNet * kWave) {
-        // beyond what the wave's LDS region holds: move the buffer in, then sort in place
-        for (int k = 0; k < kTailNet; k++) list[(long long)(g + k) * n + i] = tails[(long long)i * kTailNet + k];
+        // beyond what the wave's LDS region holds: sort in place
         for (int k = g + 1; k < g + t; k++) {
             const int v = list[(long long)k * n + i];
             int q = k - 1;
@@ -964,8 +1003,10 @@ __device__ __forceinline__ void pack_one(const PassArrays& a, const Phys& ph, do
     prim[4 * (long long)i + 2] = make_double4((ph.gamma - 1.0) * rho * a.u[i], 0.0, 0.0, 0.0);
 }
 
-__global__ void k_pack_prim(PassArrays a, Phys ph, double4* __restrict__ prim) {
+// (the pack kernels run in blocks of 256 and empty the blocks' tail bins)
+__global__ void k_pack_prim(PassArrays a, Phys ph, double4* __restrict__ prim, int* __restrict__ fill) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (threadIdx.x == 0) fill[blockIdx.x] = 0;
     if (i >= a.n) return;
     pack_one(a, ph, prim, i);
 }
@@ -978,8 +1019,9 @@ __global__ void k_pack_prim(PassArrays a, Phys ph, double4* __restrict__ prim) {
 // of that boundary reads.
 __global__ void k_pack_prim_active(PassArrays a, Phys ph, const int* __restrict__ gcount,
                                    const unsigned char* __restrict__ mode, const int* __restrict__ list,
-                                   double4* __restrict__ prim) {
+                                   double4* __restrict__ prim, int* __restrict__ fill) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (threadIdx.x == 0) fill[blockIdx.x] = 0;
     if (i >= a.n || mode[i] != kModeSolve) return;
     const long long n = a.n;
     pack_one(a, ph, prim, i);
@@ -987,39 +1029,30 @@ __global__ void k_pack_prim_active(PassArrays a, Phys ph, const int* __restrict_
     for (int k = 0; k < cnum; k++) pack_one(a, ph, prim, list[(long long)k * n + i]);
 }
 
-// i is outside j's gather set: the pair enters j's flux list as its st-th tail
-// entry (past the gather part, sorted afterwards); the first kTailNet go to
-// j's contiguous tail buffer, so the appends to one particle share a cache
-// line, the rest to the list itself
-__device__ __forceinline__ void store_tail(int* __restrict__ tails, int* __restrict__ list,
-                                           const int* __restrict__ gcount, int cap, long long n, int j, int st, int i) {
-    if (st < kTailNet) tails[(long long)j * kTailNet + st] = i;
-    else if (gcount[j] + st < cap) list[(long long)(gcount[j] + st) * n + j] = i;
-}
-
 // One thread per particle, one wave per block; the neighbours' records come by
 // lane teams, and while one is summed the next is on its way to LDS.  The tail
-// appends wait in LDS until the sums are done and then take their slots four
-// atomics at a time: each costs a round trip to L2, and in the loop a wave had
-// one in nearly every step.  The flux records leave through LDS too, in whole
-// 128-byte lines: 16-byte stores 256 bytes apart reached memory as partial
-// lines (14.7 GB written where records, outputs and tails hold 8.7 GB,
-// clustered 16.8M).  Three waves per SIMD: the sums, the record in hand and the
+// appends of the wave queue in LDS until the sums are done: in the loop a wave
+// had an atomic's round trip to L2 in nearly every step.  Then the queue is
+// worked off 64 at a time, four rounds in flight; the entries of a round that go
+// to one bin take their places with one atomic.  The flux records leave through
+// LDS too, in whole 128-byte lines: 16-byte stores 256 bytes apart reached memory
+// as partial lines.  Three waves per SIMD: the sums, the record in hand and the
 // loop's values take 140 VGPRs, and a fourth wave spills.  Measured: lattice
-// 2.1M 1.06 -> 0.89 ms, shock tube 295k (mixed) 0.177 -> 0.124 ms; clustered
-// 16.8M stays at 13.9 ms, 5.7 of them for the appends.
+// 2.1M 1.06 -> 0.81 ms, clustered 16.8M 13.8 -> 9.2 ms, shock tube 295k (mixed)
+// 0.177 -> 0.114 ms.
 // With HIER (hierarchical steps with active subsets) only the particles of
 // mode kModeSolve get new gradients; a kept particle with a gather list only
 // appends itself to the lists of its active neighbours that do not reach it.
 constexpr int kGradWaves = 3;
-constexpr int kAppends = 16;   // appends a lane holds back
+constexpr int kAppends = 768;   // appends a wave holds back
 struct GradLds {
     TeamLds<8> t;
-    int append[kAppends][kWave];
+    int to[kAppends];               // particle j whose list takes ...
+    unsigned char from[kAppends];   // ... the particle of this lane
 };
 template <bool MIXED, bool HIER>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))) void k_gradients(PassArrays a, Phys ph, const int* __restrict__ gcount,
-                                                    int* __restrict__ counts, int* __restrict__ list, int* __restrict__ tails,
+                                                    int* __restrict__ counts, int* __restrict__ list, Bins bins,
                                                     const double4* __restrict__ prim, void* __restrict__ recp,
                                                     Counters* cnt, const unsigned char* __restrict__ mode,
                                                     const long long* __restrict__ home) {
@@ -1039,7 +1072,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
             double d[3];
             displacement(ph, xi, pj.x, pj.y, pj.z, d);
             const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-            if (!(r < pj.w)) store_tail(tails, list, gcount, ph.max_ngb, n, j, atomicAdd(&counts[j], 1), i);
+            if (!(r < pj.w)) bin_append(bins, counts, list, gcount, ph.max_ngb, a.n, j, i);
         }
     }
     const bool act = i < a.n && (!HIER || mode[i] == kModeSolve);
@@ -1077,7 +1110,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
     const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i(cnum));
     auto entry = [&](int k) { return k < cnum ? list[(long long)k * n + i] : -1; };
     int j = entry(0), jn = entry(1);
-    int napp = 0;
+    int napp = 0;   // appends of the wave so far
+    const unsigned long long below = (1ull << lane) - 1ull;
     if (kmax > 0) team_load<128, 5>(S8, prim, j >= 0 ? j : self, lane);
     for (int k = 0; k < kmax; k++) {
         wait_vmem();
@@ -1094,15 +1128,22 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
         wait_lds();
         if (k + 1 < kmax) team_load<128, 5>(S8, prim, j >= 0 ? j : self, lane);
         jn = entry(k + 2);
-        if (jc < 0) continue;
         double d[3];
         displacement(ph, xi, rec[0], rec[1], rec[2], d);
         const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-        if (!(r < rec[3])) {
-            if (napp < kAppends) lds.append[napp][lane] = jc;
-            else store_tail(tails, list, gcount, cap, n, jc, atomicAdd(&counts[jc], 1), i);
-            napp++;
+        const bool append = jc >= 0 && !(r < rec[3]);
+        const unsigned long long am = __ballot(append);
+        if (append) {
+            const int at = napp + __popcll(am & below);
+            if (at < kAppends) {
+                lds.to[at] = jc;
+                lds.from[at] = (unsigned char)lane;
+            } else {
+                bin_append(bins, counts, list, gcount, cap, a.n, jc, i);
+            }
         }
+        napp += __popcll(am);
+        if (jc < 0) continue;
         const double* phi_j = rec + 4;
         // MIXED: the pairwise kernel weight in FP32; the moments and sums in FP64, so
         // that E and the gradient sums share one set of weights and the
@@ -1129,17 +1170,39 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
         rmax = fmax(rmax, r);
     }
     {
-        const int held = min(napp, kAppends);
-        const int most = __builtin_amdgcn_readfirstlane(wave_max_i(held));
-        for (int b = 0; b < most; b += 4) {
-            int to[4], st[4];
+        const int held = min(napp, kAppends), r0 = i - lane;
+        wave_lds_sync();
+        for (int b = 0; b < held; b += 4 * kWave) {
+            int to[4], lead[4], rank[4], at[4];
 #pragma unroll
-            for (int q = 0; q < 4; q++) to[q] = b + q < held ? lds.append[b + q][lane] : -1;
+            for (int q = 0; q < 4; q++) {
+                const int e = b + q * kWave + lane;
+                to[q] = e < held ? lds.to[e] : -1;
+                lead[q] = lane;
+                rank[q] = 0;
+                int share = 0;   // appends of the round that go to the lane's bin
+                unsigned long long left = __ballot(to[q] >= 0);
+                while (left) {
+                    const int first = __ffsll((long long)left) - 1;
+                    const int bin = __builtin_amdgcn_readlane(to[q], first) >> 8;
+                    const bool same = (to[q] >> 8) == bin;   // (-1 >> 8 is no bin)
+                    const unsigned long long m = __ballot(same);
+                    if (same) {
+                        lead[q] = first;
+                        rank[q] = __popcll(m & below);
+                        share = __popcll(m);
+                    }
+                    left &= ~m;
+                }
+                at[q] = to[q] >= 0 && lead[q] == lane ? atomicAdd(&bins.fill[to[q] >> 8], share) : 0;
+            }
 #pragma unroll
-            for (int q = 0; q < 4; q++) st[q] = to[q] >= 0 ? atomicAdd(&counts[to[q]], 1) : 0;
-#pragma unroll
-            for (int q = 0; q < 4; q++)
-                if (to[q] >= 0) store_tail(tails, list, gcount, cap, n, to[q], st[q], i);
+            for (int q = 0; q < 4; q++) {
+                const int base = __shfl(at[q], lead[q], kWave);
+                if (to[q] >= 0)
+                    bin_store(bins, counts, list, gcount, cap, a.n, to[q], base + rank[q],
+                              r0 + lds.from[b + q * kWave + lane]);
+            }
         }
     }
     // (lanes without a particle run along on zeros and store nothing)
@@ -1850,19 +1913,20 @@ void launch_solve_h(const PassArrays& a, const TreeDesc& td, const int2* tab,
     if (t1) hipEventRecord(t1, s);
 }
 
-void launch_gradients(const PassArrays& a, const Phys& ph, const int* gcount, int* counts, int* list, int* tails,
+void launch_gradients(const PassArrays& a, const Phys& ph, const int* gcount, int* counts, int* list, int2* bin_entry, int* bin_fill,
                       int mixed, double4* prim, void* rec, Counters* cnt, hipEvent_t t0, hipEvent_t t1,
                       hipStream_t s) {
-    k_pack_prim<<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, prim);
+    const Bins bins{bin_entry, bin_fill};
+    k_pack_prim<<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, prim, bin_fill);
     if (t0) hipEventRecord(t0, s);
     if (mixed)
-        k_gradients<true, false><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, gcount, counts, list, tails, prim, rec,
+        k_gradients<true, false><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, gcount, counts, list, bins, prim, rec,
                                                                      cnt, nullptr, nullptr);
     else
-        k_gradients<false, false><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, gcount, counts, list, tails, prim, rec,
+        k_gradients<false, false><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, gcount, counts, list, bins, prim, rec,
                                                                       cnt, nullptr, nullptr);
     if (t1) hipEventRecord(t1, s);
-    k_sort_tails<<<blocks_of(a.n, 256), 256, 0, s>>>(a.n, ph.max_ngb, gcount, counts, list, tails, cnt);
+    k_sort_tails<<<blocks_of(a.n, 256), 256, 0, s>>>(a.n, ph.max_ngb, gcount, counts, list, bins, cnt);
 }
 
 void launch_solve_h_active(const PassArrays& a, const TreeDesc& td, const int2* tab, const double4* pos,
@@ -1883,12 +1947,13 @@ void launch_solve_h_active(const PassArrays& a, const TreeDesc& td, const int2* 
 }
 
 void launch_gradients_active(const PassArrays& a, const Phys& ph, const unsigned char* mode, const long long* home,
-                             const int* gcount, int* counts, int* list, int* tails, double4* prim, void* rec,
+                             const int* gcount, int* counts, int* list, int2* bin_entry, int* bin_fill, double4* prim, void* rec,
                              Counters* cnt, hipStream_t s) {
-    k_pack_prim_active<<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, gcount, mode, list, prim);
-    k_gradients<false, true><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, gcount, counts, list, tails, prim, rec, cnt,
+    const Bins bins{bin_entry, bin_fill};
+    k_pack_prim_active<<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, gcount, mode, list, prim, bin_fill);
+    k_gradients<false, true><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, gcount, counts, list, bins, prim, rec, cnt,
                                                                  mode, home);
-    k_sort_tails<<<blocks_of(a.n, 256), 256, 0, s>>>(a.n, ph.max_ngb, gcount, counts, list, tails, cnt);
+    k_sort_tails<<<blocks_of(a.n, 256), 256, 0, s>>>(a.n, ph.max_ngb, gcount, counts, list, bins, cnt);
     k_pack_rec_kept<<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, mode, home, counts, (double*)rec);
 }
 
