@@ -93,6 +93,14 @@ __device__ __forceinline__ T spline_w(T q) {
     return T(2) * (t * t) * t - T(8) * (u * u) * u;
 }
 
+// dw/dq
+template <typename T>
+__device__ __forceinline__ T spline_dw(T q) {
+    const T t = spline_pos(T(1) - q);
+    const T u = spline_pos(T(0.5) - q);
+    return T(24) * (u * u) - T(6) * (t * t);
+}
+
 // q * dw/dq
 template <typename T>
 __device__ __forceinline__ T spline_qdw(T q) {
@@ -259,6 +267,25 @@ __device__ __forceinline__ void team_load(TeamLds<C>& S, const void* __restrict_
         if (USED == C || c < USED)
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
                                              (__attribute__((address_space(3))) void*)(S.rec + q * kWave), 16, 0, 0);
+    }
+}
+
+// The other way: the lanes put the chunks of their records (team_put), then C
+// neighbouring lanes store one record's chunks side by side, to base + STRIDE r
+// for the lanes r whose bit is set in `lanes`.
+template <int C>
+__device__ __forceinline__ void team_put(TeamLds<C>& S, int c, int lane, const uint4& u) {
+    S.rec[lane * C + ((c + lane) & (C - 1))] = u;
+}
+template <int STRIDE, int C>
+__device__ __forceinline__ void team_store(const TeamLds<C>& S, void* __restrict__ base, unsigned long long lanes,
+                                           int lane) {
+    constexpr int kTeams = kWave / C;
+    const int team = lane / C, p = lane % C;
+#pragma unroll
+    for (int q = 0; q < C; q++) {
+        const int r = kTeams * q + team, c = (p - r) & (C - 1);
+        if ((lanes >> r) & 1) *(uint4*)((char*)base + r * STRIDE + c * 16) = S.rec[q * kWave + lane];
     }
 }
 

@@ -140,15 +140,19 @@ void launch_hier_finish(int n, const double* m, const double* vx, const double* 
 
 // adjoint.hip
 // Adjoint scratch, doubles per particle: 0-27 pass accumulators, 28-55 step
-// reverse, then the per-particle records the pass reverse pulls through the
-// flux lists (kAdjRec) and its own-side terms (kAdjOwn), then the limiter
-// terms part one addresses to single neighbours (kAdjLim: 16 int32 indices and
-// 12 values per particle).
-constexpr int kAdjRec = 36;
+// reverse, then the per-particle records the pass reverse gathers through the
+// flux lists (kAdjRec), the adjoints of dp and dE (kAdjLam), the neighbour
+// records of its gather loops (kAdjNgb), its own-side terms (kAdjOwn), and the
+// limiter terms part one addresses to single neighbours (kAdjLim: a 64-byte line
+// of indices and 12 values per particle).  The records start on whole 128-byte
+// lines for an even capacity.
+constexpr int kAdjRec = 32;
+constexpr int kAdjNgb = 16;
+constexpr int kAdjLam = 4;
 constexpr int kAdjOwn = 8;
 constexpr int kAdjLim = 20;
 constexpr int kAdjPullOffset = 56;
-constexpr int kAdjSlots = kAdjPullOffset + kAdjRec + kAdjOwn + kAdjLim;
+constexpr int kAdjSlots = kAdjPullOffset + kAdjRec + kAdjNgb + kAdjLam + kAdjOwn + kAdjLim;
 
 void launch_pass_adjoint(const PassArrays& a, const Phys& ph, const int* counts, const int* gcount,
                          const int* list, const double* lam_dp, const double* lam_dE, double* scratch,

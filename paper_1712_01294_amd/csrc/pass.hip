@@ -1315,7 +1315,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
         // the wave's records, 128 bytes of each at a time, transposed in LDS: eight
         // lanes then store one record's line
         const unsigned long long stored = __ballot(act);
-        const int r0 = i - lane, team = lane / 8;
 #pragma unroll
         for (int h = 0; h < (int)sizeof(T) / 4; h++) {
             wave_lds_sync();
@@ -1323,17 +1322,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
             for (int c = 0; c < 8; c++) {
                 uint4 u;
                 __builtin_memcpy(&u, v + (8 * h + c) * (16 / sizeof(T)), 16);
-                S8.rec[lane * 8 + ((c + lane) & 7)] = u;
+                team_put(S8, c, lane, u);
             }
             wave_lds_sync();
-            const int c = (lane - team) & 7;   // the chunk at this lane's slots
-#pragma unroll
-            for (int q = 0; q < 8; q++) {
-                const int r = 8 * q + team;
-                const uint4 u = S8.rec[q * kWave + lane];
-                if ((stored >> r) & 1)
-                    *(uint4*)((char*)recp + (size_t)(unsigned)(r0 + r) * (32 * sizeof(T)) + 128 * h + 16 * c) = u;
-            }
+            team_store<32 * sizeof(T)>(S8, (char*)recp + (size_t)(unsigned)(i - lane) * (32 * sizeof(T)) + 128 * h,
+                                       stored, lane);
         }
     }
     count_add(&cnt->illcond, ill);
