@@ -339,7 +339,7 @@ __device__ __forceinline__ unsigned long long dilated_sub(unsigned long long x, 
 // per-wave LDS of the cell enumeration: per axis and offset t = 0..63 from the
 // range's first cell, the key bits of the cell coordinate with its periodic
 // image in the top bits (2 per axis: shift + 1 in box sides), and its squared
-// distance from the box (rounded down)
+// distance from the box in units of the scan radius (rounded down)
 constexpr int kImageBit = 58;
 struct ScanLds {
     unsigned long long key[3][kWave];
@@ -517,6 +517,9 @@ __device__ __forceinline__ void scan_cells(const TreeDesc& td, const int2* __res
     wrap = __builtin_amdgcn_readfirstlane(wrap);
     if (cnt[0] <= 0 || cnt[1] <= 0 || cnt[2] <= 0) return;
     const int ncells = cnt[0] * cnt[1] * cnt[2];
+    // slack for the rounding of cell edges, of the keys' quantisation and of the distances in FP32
+    const double Rg = Rq * (1.0 + 1e-9) + 1e-12 * fmax(td.box[0], fmax(td.box[1], td.box[2])), iRg = 1.0 / Rg;
+    const float Rg2 = 1.000001f;
     wave_lds_sync();
 #pragma unroll
     for (int d = 0; d < 3; d++) {
@@ -526,12 +529,10 @@ __device__ __forceinline__ void scan_cells(const TreeDesc& td, const int2* __res
         const double s = td.cs[L][d], clo = u * s;
         const double g = (wrap >> d) & 1 ? 0.0 : fmax(0.0, fmax(clo - bmax[d], bmin[d] - (clo + s)));
         S.key[d][lane] = deposit_bits((unsigned)u & (nc - 1), td.mask[L][d]) | (image << (kImageBit + 2 * d));
-        S.dist2[d][lane] = (float)(g * g) * 0.9999998f;
+        const float q = (float)(g * iRg);
+        S.dist2[d][lane] = q * q * 0.9999998f;
     }
     wave_lds_sync();
-    // slack for the rounding of cell edges, of the keys' quantisation and of the distances in FP32
-    const double Rg = Rq * (1.0 + 1e-9) + 1e-12 * fmax(td.box[0], fmax(td.box[1], td.box[2]));
-    const float Rg2 = (float)(Rg * Rg) * 1.000001f;
     const int2* __restrict__ cells = tab + td.tab_off[L];
     // cell coordinates from the flat index through FP32 reciprocals (exact for
     // the few thousand cells a scan covers)
