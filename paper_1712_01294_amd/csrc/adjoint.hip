@@ -374,8 +374,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kAdjPairWave
     auto entry = [&](int k) { return k < cnum ? list[(long long)k * n + i] : -1; };
     auto start = [&](int j) {
         const int jr = j >= 0 ? j : self;
-        team_load<8 * kAdjRec, 16>(S.other, ar.rec, jr, lane);
-        team_load<8 * kAdjLam, 2>(S.lam, ar.lam, jr, lane);
+        team_load<8 * kAdjRec, 16>(S.other, ar.rec, a.n, jr, lane);
+        team_load<8 * kAdjLam, 2>(S.lam, ar.lam, a.n, jr, lane);
     };
     double li[4];
     {
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kAdjPairWave
     }
     int j = entry(0), jn = entry(1);
     if (kmax > 0) {
-        team_load<8 * kAdjRec, 16>(S.own, ar.rec, self, lane);
+        team_load<8 * kAdjRec, 16>(S.own, ar.rec, a.n, self, lane);
         start(j);
     }
     for (int k = 0; k < kmax; k++) {
@@ -537,7 +537,7 @@ __global__ __launch_bounds__(64) void k_adj_grad_own(PassArrays a, Phys ph, cons
     // the index of the one after to a register; body(j, x (3), rho, v (3), P)
     auto walk = [&](auto&& body) {
         int j = entry(0), jn = entry(1);
-        if (kmax > 0) team_load<8 * kAdjNgb, 5>(S8, ar.ngb, j >= 0 ? j : i, lane);
+        if (kmax > 0) team_load<8 * kAdjNgb, 5>(S8, ar.ngb, a.n, j >= 0 ? j : i, lane);
         for (int k = 0; k < kmax; k++) {
             wait_vmem();
             wave_lds_sync();
@@ -547,7 +547,7 @@ __global__ __launch_bounds__(64) void k_adj_grad_own(PassArrays a, Phys ph, cons
             j = jn;
             wave_lds_sync();
             wait_lds();
-            if (k + 1 < kmax) team_load<8 * kAdjNgb, 5>(S8, ar.ngb, j >= 0 ? j : i, lane);
+            if (k + 1 < kmax) team_load<8 * kAdjNgb, 5>(S8, ar.ngb, a.n, j >= 0 ? j : i, lane);
             jn = entry(k + 2);
             if (jc >= 0) body(jc, rc);
         }
@@ -762,8 +762,8 @@ __global__ __launch_bounds__(64) void k_adj_grad_pull(PassArrays a, Phys ph, con
     auto entry = [&](int k) { return k < cnum ? list[(long long)k * n + j] : -1; };
     auto start = [&](int i) {
         const int ir = i >= 0 ? i : j;
-        team_load<8 * kAdjRec, 16>(S.rec, pa.rec, ir, lane);
-        team_load<64, 4>(S.lix, pa.lix, ir, lane);
+        team_load<8 * kAdjRec, 16>(S.rec, pa.rec, a.n, ir, lane);
+        team_load<64, 4>(S.lix, pa.lix, a.n, ir, lane);
     };
     int i = entry(0), inext = entry(1);
     if (kmax > 0) start(i);
@@ -866,7 +866,7 @@ __global__ __launch_bounds__(64) void k_adj_length(PassArrays a, Phys ph, const 
     const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i(cnum));
     auto entry = [&](int k) { return k < cnum ? list[(long long)k * n + j] : -1; };
     int i = entry(0), inext = entry(1);
-    if (kmax > 0) team_load<8 * kLenRec, 3>(S, pa.len, i >= 0 ? i : j, lane);
+    if (kmax > 0) team_load<8 * kLenRec, 3>(S, pa.len, a.n, i >= 0 ? i : j, lane);
     for (int k = 0; k < kmax; k++) {
         wait_vmem();
         wave_lds_sync();
@@ -876,7 +876,7 @@ __global__ __launch_bounds__(64) void k_adj_length(PassArrays a, Phys ph, const 
         i = inext;
         wave_lds_sync();
         wait_lds();
-        if (k + 1 < kmax) team_load<8 * kLenRec, 3>(S, pa.len, i >= 0 ? i : j, lane);
+        if (k + 1 < kmax) team_load<8 * kLenRec, 3>(S, pa.len, a.n, i >= 0 ? i : j, lane);
         inext = entry(k + 2);
         if (ic < 0) continue;
         const double xi[3] = {rc[0], rc[1], rc[2]};

@@ -76,6 +76,49 @@ __device__ __forceinline__ Counters* counter_copy(Counters* base) {
     return (Counters*)((char*)base + (blockIdx.x & (kCounterCopies - 1)) * kCounterStride);
 }
 
+// sqrt(x) for 0 <= x far from the ends of the exponent range (a squared
+// distance): the steps of the correctly rounded sqrt without its rescaling of
+// arguments below 2^-767
+__device__ __forceinline__ double sqrt_mid(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, x), h, g);
+    g = fma(fma(-g, g, x), h, g);
+    return x > 0.0 ? g : 0.0;
+}
+
+// 2^-700 <= x < 2^700
+__device__ __forceinline__ bool is_mid(double x) {
+    return (unsigned)__double2hiint(x) - (323u << 20) < (1400u << 20);
+}
+
+// sqrt(x) and 1/sqrt(x) together for x as in is_mid (the correctly rounded
+// sqrt's steps, its half reciprocal refined once more: 12 instructions against 33
+// of a square root and a division; the reciprocal is within 1.5 ulp)
+__device__ __forceinline__ double sqrt_inv_mid(double x, double& inv) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, x), h, g);
+    const double e = fma(-h, g, 0.5);
+    g = fma(fma(-g, g, x), h, g);
+    inv = 2.0 * fma(h, e, h);
+    return g;
+}
+
+// the same for every x
+__device__ __forceinline__ double sqrt_inv(double x, double& inv) {
+    if (__builtin_expect(is_mid(x), 1)) return sqrt_inv_mid(x, inv);
+    const double g = sqrt(x);
+    inv = 1.0 / g;
+    return g;
+}
+
 // ---------------------------------------------------------------- kernel
 // Cubic spline with support radius H: W = 8/(pi H^3) w(q), q = r/H,
 // w = 1 - 6q^2 + 6q^3 (q <= 1/2), 2(1-q)^3 (1/2 < q <= 1), 0 beyond.
@@ -247,10 +290,14 @@ struct TeamLds {
 __device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xc07f); }
 __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0f70); }
 
-// starts the loads of records j (one per lane, all 64 lanes); the earlier
-// records' reads must have returned.  Chunks from USED on are left out.
+// starts the loads of records j (one per lane, all 64 lanes) of the n records at
+// base; the earlier records' reads must have returned.  Chunks from USED on are
+// left out.  Up to 4 GiB of records are addressed by 32-bit offsets (one
+// instruction a load instead of four).
 template <int STRIDE, int USED, int C>
-__device__ __forceinline__ void team_load(TeamLds<C>& S, const void* __restrict__ base, int j, int lane) {
+__device__ __forceinline__ void team_load(TeamLds<C>& S, const void* __restrict__ base, int n, int j, int lane) {
+    typedef __attribute__((address_space(3))) uint4 LdsChunk;
+    typedef __attribute__((address_space(1))) char Global;
     constexpr int kTeams = kWave / C;
     S.idx[(lane % kTeams) * C + lane / kTeams] = j;
     wave_lds_sync();
@@ -260,13 +307,24 @@ __device__ __forceinline__ void team_load(TeamLds<C>& S, const void* __restrict_
     for (int q = 0; q < C; q++) js[q] = S.idx[team * C + q];
     wave_lds_sync();
     wait_lds();
+    LdsChunk* to = (LdsChunk*)S.rec;
+    const Global* from = (const Global*)base;
+    if ((unsigned long long)n * STRIDE <= 1ull << 32) {
 #pragma unroll
-    for (int q = 0; q < C; q++) {
-        const int r = kTeams * q + team, c = (p - r) & (C - 1);
-        const char* g = (const char*)base + (size_t)(unsigned)js[q] * STRIDE + c * 16;
-        if (USED == C || c < USED)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
-                                             (__attribute__((address_space(3))) void*)(S.rec + q * kWave), 16, 0, 0);
+        for (int q = 0; q < C; q++) {
+            const int c = (p - kTeams * q - team) & (C - 1);
+            if (USED == C || c < USED)
+                __builtin_amdgcn_global_load_lds(from + ((unsigned)js[q] * (unsigned)STRIDE + (unsigned)c * 16u),
+                                                 to + q * kWave, 16, 0, 0);
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < C; q++) {
+            const int c = (p - kTeams * q - team) & (C - 1);
+            if (USED == C || c < USED)
+                __builtin_amdgcn_global_load_lds(from + ((size_t)(unsigned)js[q] * STRIDE + c * 16), to + q * kWave, 16,
+                                                 0, 0);
+        }
     }
 }
 
@@ -577,20 +635,6 @@ __device__ __forceinline__ void scan_cells(const TreeDesc& td, const int2* __res
             wave_lds_sync();   // the next chunk overwrites the owners
         }
     }
-}
-
-// sqrt(x) for 0 <= x far from the ends of the exponent range (a squared
-// distance): the steps of the correctly rounded sqrt without its rescaling of
-// arguments below 2^-767
-__device__ __forceinline__ double sqrt_mid(double x) {
-    const double y = __builtin_amdgcn_rsq(x);
-    double g = x * y, h = 0.5 * y;
-    const double r = fma(-h, g, 0.5);
-    g = fma(g, r, g);
-    h = fma(h, r, h);
-    g = fma(fma(-g, g, x), h, g);
-    g = fma(fma(-g, g, x), h, g);
-    return x > 0.0 ? g : 0.0;
 }
 
 // The lanes one group scan serves: of the lanes that still need one, those with

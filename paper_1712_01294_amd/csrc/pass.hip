@@ -1112,7 +1112,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
     int j = entry(0), jn = entry(1);
     int napp = 0;   // appends of the wave so far
     const unsigned long long below = (1ull << lane) - 1ull;
-    if (kmax > 0) team_load<128, 5>(S8, prim, j >= 0 ? j : self, lane);
+    if (kmax > 0) team_load<128, 5>(S8, prim, a.n, j >= 0 ? j : self, lane);
     for (int k = 0; k < kmax; k++) {
         wait_vmem();
         wave_lds_sync();
@@ -1126,7 +1126,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
         j = jn;
         wave_lds_sync();
         wait_lds();
-        if (k + 1 < kmax) team_load<128, 5>(S8, prim, j >= 0 ? j : self, lane);
+        if (k + 1 < kmax) team_load<128, 5>(S8, prim, a.n, j >= 0 ? j : self, lane);
         jn = entry(k + 2);
         double d[3];
         displacement(ph, xi, rec[0], rec[1], rec[2], d);
@@ -1511,6 +1511,25 @@ __device__ __forceinline__ T pair_limit(T f, T pk, T po) {
     return pk == po ? pk : s * r;
 }
 
+// the sound speeds sqrt(gp / rho) of the two sides; in FP64 as gp / sqrt(gp rho),
+// one reciprocal square root in place of a division and a square root
+__device__ __forceinline__ void sound_speeds(double gpL, double rL, double gpR, double rR, double& cL, double& cR) {
+    const double xL = gpL * rL, xR = gpR * rR;
+    if (__builtin_expect(is_mid(xL) && is_mid(xR), 1)) {
+        sqrt_inv_mid(xL, cL);
+        sqrt_inv_mid(xR, cR);
+        cL *= gpL;
+        cR *= gpR;
+    } else {
+        cL = sqrt(gpL / rL);
+        cR = sqrt(gpR / rR);
+    }
+}
+__device__ __forceinline__ void sound_speeds(float gpL, float rL, float gpR, float rR, float& cL, float& cR) {
+    cL = sqrtf(gpL / rL);
+    cR = sqrtf(gpR / rR);
+}
+
 template <typename T, bool MFV, bool LIM>
 __device__ __forceinline__ PairOut<T> pair_flux(const T* __restrict__ m, const T* __restrict__ o, bool mL,
                                                 const T d[3], T r, T gamma) {
@@ -1529,9 +1548,16 @@ __device__ __forceinline__ PairOut<T> pair_flux(const T* __restrict__ m, const T
     T A[3];
 #pragma unroll
     for (int c = 0; c < 3; c++) A[c] = add_rn(mul_rn(km, tm[c]), mul_rn(ko, to[c]));
-    const T Amag = tsqrt(A[0] * A[0] + A[1] * A[1] + A[2] * A[2]);
-    if (!(Amag > T(0))) return out;
-    const T iA = T(1) / Amag;
+    const T A2 = A[0] * A[0] + A[1] * A[1] + A[2] * A[2];
+    T Amag, iA;
+    if constexpr (sizeof(T) == 8) {
+        if (!(A2 > T(0))) return out;
+        Amag = sqrt_inv(A2, iA);
+    } else {
+        Amag = tsqrt(A2);
+        if (!(Amag > T(0))) return out;
+        iA = T(1) / Amag;
+    }
     const T nh[3] = {A[0] * iA, A[1] * iA, A[2] * iA};
 
     // midpoint reconstruction of rho, vx, vy, vz, P on each side
@@ -1585,7 +1611,8 @@ __device__ __forceinline__ PairOut<T> pair_flux(const T* __restrict__ m, const T
     const T uL = (qL[1] - w[0]) * nh[0] + (qL[2] - w[1]) * nh[1] + (qL[3] - w[2]) * nh[2];
     const T uR = (qR[1] - w[0]) * nh[0] + (qR[2] - w[1]) * nh[1] + (qR[3] - w[2]) * nh[2];
     const T rL = qL[0], pL = qL[4], rR = qR[0], pR = qR[4];
-    const T cL = tsqrt(gamma * pL / rL), cR = tsqrt(gamma * pR / rR);
+    T cL, cR;
+    sound_speeds(gamma * pL, rL, gamma * pR, rR, cL, cR);
     const T SL = (uL - cL < uR - cR) ? uL - cL : uR - cR;
     const T SR = (uL + cL > uR + cR) ? uL + cL : uR + cR;
     const T mLf = rL * (SL - uL), mRf = rR * (SR - uR);
@@ -1723,8 +1750,8 @@ __device__ __forceinline__ void fluxes_body(const PassArrays& a, const Phys& ph,
     auto start = [&](bool on, int j) {
         if (LEV && !__ballot(on)) return;
         const int jr = on ? j : self;
-        team_load<32 * sizeof(T), 2 * sizeof(T)>(S.rec, rec, jr, lane);
-        if constexpr (sizeof(T) == 4) team_load<128, 2>(S.pos, prim, jr, lane);
+        team_load<32 * sizeof(T), 2 * sizeof(T)>(S.rec, rec, a.n, jr, lane);
+        if constexpr (sizeof(T) == 4) team_load<128, 2>(S.pos, prim, a.n, jr, lane);
     };
     int j = entry(0), jn = entry(1);
     int lj = LEV ? level(j) : 0;
@@ -1761,13 +1788,19 @@ __device__ __forceinline__ void fluxes_body(const PassArrays& a, const Phys& ph,
         if (!on) continue;
         double dij[3];
         displacement(ph, xi, xj[0], xj[1], xj[2], dij);   // x_j - x_i
-        const double r = sqrt(dij[0] * dij[0] + dij[1] * dij[1] + dij[2] * dij[2]);
+        const double r2 = dij[0] * dij[0] + dij[1] * dij[1] + dij[2] * dij[2];
+        double r, ir;
+        if constexpr (sizeof(T) == 8)
+            r = sqrt_inv(r2, ir);
+        else
+            r = sqrt(r2);
         const bool iL = i < jc;
         // signal speed over the flux neighbours (the due ones in the levelled pass)
         auto signal = [&]() {
             const double cj = (double)rj[R_C];
-            const double proj = -((vi[0] - (double)rj[R_V0]) * dij[0] + (vi[1] - (double)rj[R_V0 + 1]) * dij[1] +
-                                  (vi[2] - (double)rj[R_V0 + 2]) * dij[2]) / r;
+            const double vd = (vi[0] - (double)rj[R_V0]) * dij[0] + (vi[1] - (double)rj[R_V0 + 1]) * dij[1] +
+                              (vi[2] - (double)rj[R_V0 + 2]) * dij[2];
+            const double proj = sizeof(T) == 8 ? -vd * ir : -vd / r;
             vs = fmax(vs, ci + cj - fmin(proj, 0.0));
         };
         // canonical displacement x_R - x_L: the minimum image commutes with
@@ -1837,7 +1870,8 @@ __device__ __forceinline__ void fluxes_body(const PassArrays& a, const Phys& ph,
 // Blocks of one wave: a block's LDS (16.3 KB FP64, 10.5 KB FP32) is free again
 // as soon as its wave ends.  The FP64 form runs at two waves per SIMD (its two
 // records alone are 128 VGPRs), the FP32 form at three.  Measured: FP64 MFM,
-// lattice 2.1M 1.84 -> 1.18 ms, clustered 16.8M 19.4 -> 15.7 ms; mixed MFM,
+// lattice 2.1M 1.84 -> 1.2 ms, clustered 16.8M 19.4 -> 14.0 ms (15.7 before the
+// 32-bit record offsets and the square roots with their reciprocals); mixed MFM,
 // shock tube 295k 0.232 -> 0.181 ms; limited FP64, clustered 2.1M 4.35 -> 3.47
 // ms; levelled, hierarchical step of 2.1M 0.89 -> 0.69 ms a launch.
 constexpr int kFlux64Waves = 2;
