@@ -126,7 +126,7 @@ typedef struct {
     int64_t first_bad;       /* lowest particle index flagged by any of the above   */
     double cond_max_seen;    /* largest ||E||_F ||B||_F                             */
     int64_t h_rounds_max;    /* most neighbour scans one kernel-length solve needed */
-    int64_t h_fallback;      /* particles solved one wave each after the group scan */
+    int64_t h_fallback;      /* particles solved one wave each (small sets: all)    */
     int64_t h_rounds3;       /* particles whose solve needed three or more scans    */
     int64_t gather_entries;  /* gather-set entries of the last solve_h, self excluded */
     int64_t h_rescan;        /* particles the rescanning kernel-length solver took   */

@@ -221,6 +221,39 @@ __device__ __forceinline__ T wave_reduce(T v, Op op) {
     return op(a.value(), b.value());
 }
 
+// the sums of u and v at once, each in the order of a sum of its own: after the
+// first step the lower half of the wave carries u and the upper half v
+__device__ __forceinline__ void wave_sum2_d(double u, double v, double& su, double& sv) {
+    using W = Words<double>;
+    W a = W::of(u), b = W::of(v);
+#pragma unroll
+    for (int k = 0; k < W::n; k++) swap_halves(a.w[k], b.w[k]);
+    a = b = W::of(a.value() + b.value());
+#pragma unroll
+    for (int k = 0; k < W::n; k++) swap_rows(a.w[k], b.w[k]);
+    a = W::of(a.value() + b.value());
+#pragma unroll
+    for (int k = 0; k < W::n; k++) b.w[k] = lane_move<0x128>(a.w[k]);
+    a = W::of(a.value() + b.value());
+#pragma unroll
+    for (int k = 0; k < W::n; k++) b.w[k] = lane_move<0x124>(a.w[k]);
+    a = W::of(a.value() + b.value());
+#pragma unroll
+    for (int k = 0; k < W::n; k++) b.w[k] = lane_move<0x4e>(a.w[k]);
+    a = W::of(a.value() + b.value());
+#pragma unroll
+    for (int k = 0; k < W::n; k++) b.w[k] = lane_move<0xb1>(a.w[k]);
+    a = W::of(a.value() + b.value());
+    Words<double> lo, hi;
+#pragma unroll
+    for (int k = 0; k < W::n; k++) {
+        lo.w[k] = (unsigned)__builtin_amdgcn_readlane((int)a.w[k], 0);
+        hi.w[k] = (unsigned)__builtin_amdgcn_readlane((int)a.w[k], 32);
+    }
+    su = lo.value();
+    sv = hi.value();
+}
+
 __device__ __forceinline__ double wave_sum_d(double v) {
     return wave_reduce(v, [](double a, double b) { return a + b; });
 }

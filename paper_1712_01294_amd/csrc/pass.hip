@@ -6,6 +6,7 @@
 // particles with the lower index as the left state, so both copies are
 // bitwise equal and the accumulated momentum and energy cancel exactly pair
 // by pair; there are no atomics on outputs and results are deterministic.
+#include <algorithm>
 #include <limits.h>
 #include <math.h>
 
@@ -454,8 +455,53 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kRootWaves)
 }
 
 
-// Particles the group scan hands over, one wave each.  The wave scans the cells
-// within a trial radius once and keeps every radius and index within it in
+// Small sets skip the group scan: every particle starts with its guess as the
+// first trial radius and goes to the list solver, one wave each.  Up to
+// kDirectMax particles the group scan has too few waves to fill the chip (one
+// per 64 particles, for 1,024 SIMDs), and the time is that of one wave's serial
+// work: on clustered sets pass after pass over the wave's mixed radii.
+// Measured (solve stage, group scan against this way, cold): lattice 4,096
+// 89 / 37 us, 13,824 186 / 68, 32,768 89 / 115 (cells and waves aligned), 46,656
+// 172 / 161, 64,000 176 / 198; random 46,656 230 / 153, 64,000 253 / 198;
+// clustered 4,096 1,098 / 96, 32,768 764 / 205, 64,000 909 / 446.  The line is
+// where an even set's time is the same both ways.
+constexpr int kDirectMax = 49152;
+template <bool HIER>
+__global__ __launch_bounds__(256) void k_solve_start(PassArrays a, TreeDesc td, const int2* __restrict__ tab,
+                                                     const unsigned long long* __restrict__ keys, Phys ph,
+                                                     double* __restrict__ hand, int* __restrict__ fb_list,
+                                                     unsigned long long* __restrict__ fb_count,
+                                                     unsigned long long* __restrict__ fb2_count,
+                                                     const unsigned char* __restrict__ mode) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    const bool act = i < a.n && (!HIER || mode[i] == kModeSolve);
+    const long long n = a.n;
+    const double H0 = act ? a.H[i] : 0.0;
+    const bool warm = H0 > 0.0;
+    double guess = H0;
+    if (__ballot(act && !warm)) {
+        const double g = cold_guess(td, tab, act ? keys[i] : 0ull, act && !warm, ph.n_ngb, a.n);
+        if (!warm) guess = g;
+    }
+    int slot = i;
+    if (HIER) {
+        const unsigned long long m = __ballot(act);
+        unsigned long long base = 0;
+        if (m && (threadIdx.x & (kWave - 1)) == 0) base = atomicAdd(fb_count, (unsigned long long)__popcll(m));
+        slot = __shfl((int)base, 0, kWave) + __popcll(m & ((1ull << (threadIdx.x & (kWave - 1))) - 1ull));
+    } else if (i == 0) {
+        *fb_count = (unsigned long long)n;
+        *fb2_count = 0ull;
+    }
+    if (!act) return;
+    fb_list[slot] = i;
+    hand[i] = 0.0;
+    hand[n + i] = INFINITY;
+    hand[2 * n + i] = (warm ? kWarmPad : kColdPad) * guess;
+}
+
+// Particles the group scan hands over (and all of a small set), one wave each.
+// The wave scans the cells within a trial radius once and keeps every radius and index within it in
 // registers (entry e on lane e mod 64, slot e / 64, scan order), narrows the
 // bracket with the weighted count at that radius, and once the radius brackets
 // the root with every radius kept, runs Newton on them with wave-wide sums in
@@ -466,7 +512,7 @@ constexpr int kWaveScans = 16;
 // At five waves per SIMD 5,120 waves are resident; 32,768 single-wave blocks
 // (about 87 particles each on the clustered set) balance the end of the
 // launch better than 16,384 (45.2 -> 44.5 ms for the solve stage).
-constexpr int kWaveBlocks = 32768;   // waves of the list solver, striding over its particles
+constexpr int kWaveBlocks = 32768;   // waves of the list solver at most, striding over its particles
 // a single sphere's scan enumerates its cells at a coarser level than a group's
 constexpr double kWaveScanScale = 0.5;
 
@@ -482,7 +528,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveSolveWa
                                                       int* __restrict__ gcount, int* __restrict__ counts,
                                                       int* __restrict__ fb2_list,
                                                       unsigned long long* __restrict__ fb2_count,
-                                                      const double* __restrict__ pad) {
+                                                      const double* __restrict__ pad, int scanned) {
     cnt = counter_copy(cnt);
     __shared__ ScanLds S;
     const int lane = threadIdx.x;
@@ -588,8 +634,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveSolveWa
                         s += spline_w(q);
                         sq += spline_qdw(q);
                     }
-                s = uniform_d(wave_sum_d(s));
-                sq = uniform_d(wave_sum_d(sq));
+                wave_sum2_d(s, sq, s, sq);
                 if (newton_step(c32 * s - ph.n_ngb, -c32 * sq * iH, lo, hi, Hc)) {
                     conv = true;
                     break;
@@ -637,12 +682,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveSolveWa
         }
         iters_max = max(iters_max, iters - iters0);
         scans_max = max(scans_max, (unsigned long long)scans);
-        many += (1 + scans >= 3) ? 1ull : 0ull;
+        many += (scanned + scans >= 3) ? 1ull : 0ull;
     }
     if (lane == 0) {
         if (iters) atomicAdd(&cnt->h_iters, iters);
         if (iters_max) atomicMax(&cnt->h_iters_max, iters_max);
-        if (scans_max) atomicMax(&cnt->h_rounds_max, 1 + scans_max);
+        if (scans_max) atomicMax(&cnt->h_rounds_max, scanned + scans_max);
         if (many) atomicAdd(&cnt->h_rounds3, many);
         if (over) atomicAdd(&cnt->overflow, over);
     }
@@ -689,8 +734,7 @@ __global__ __launch_bounds__(64) void k_solve_h_fallback(PassArrays a, TreeDesc 
                     sq += spline_qdw(qq);
                 }
             });
-            s = uniform_d(wave_sum_d(s));
-            sq = uniform_d(wave_sum_d(sq));
+            wave_sum2_d(s, sq, s, sq);
             f = c32 * s - ph.n_ngb;
             fp = -c32 * sq * iH;
             nk = kernel_norm(H) * s;
@@ -1925,18 +1969,26 @@ void launch_solve_h(const PassArrays& a, const TreeDesc& td, const int2* tab,
                     int* gcount,
                     int* counts, int* fb_list, unsigned long long* fb_count, int* fb2_list,
                     unsigned long long* fb2_count, hipEvent_t t0, hipEvent_t t1, hipStream_t s) {
-    launch_fill_u64(1, fb_count, 0ull, s);
-    launch_fill_u64(1, fb2_count, 0ull, s);
+    const bool direct = a.n <= kDirectMax;
+    if (!direct) {
+        launch_fill_u64(1, fb_count, 0ull, s);
+        launch_fill_u64(1, fb2_count, 0ull, s);
+    }
     if (t0) hipEventRecord(t0, s);
-    k_solve_h<false><<<blocks_of(a.n, 256), 256, 0, s>>>(a, td, tab, pos, keys, ph, cnt, rl, list, gcount, counts,
-                                                         fb_list, fb_count, nullptr, nullptr);
-    k_root_h<false><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph.n_ngb, ph.h_maxit, cnt, rl, list, gcount, counts, fb_list,
-                                                        fb_count, nullptr);
+    if (direct) {
+        k_solve_start<false><<<blocks_of(a.n, 256), 256, 0, s>>>(a, td, tab, keys, ph, rl, fb_list, fb_count, fb2_count,
+                                                                 nullptr);
+    } else {
+        k_solve_h<false><<<blocks_of(a.n, 256), 256, 0, s>>>(a, td, tab, pos, keys, ph, cnt, rl, list, gcount, counts,
+                                                             fb_list, fb_count, nullptr, nullptr);
+        k_root_h<false><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph.n_ngb, ph.h_maxit, cnt, rl, list, gcount, counts,
+                                                            fb_list, fb_count, nullptr);
+    }
     // one wave per handed-over particle, striding over the count left on the device
-    k_solve_h_wave<<<kWaveBlocks, 64, 0, s>>>(a, td, tab, pos, ph, cnt, fb_list, fb_count, rl, list, gcount,
-                                              counts, fb2_list, fb2_count, nullptr);
-    k_solve_h_fallback<<<kFallbackWaves, 64, 0, s>>>(a, td, tab, pos, ph, cnt, fb2_list, fb2_count, list, gcount,
-                                                     counts, nullptr);
+    k_solve_h_wave<<<std::min(a.n, kWaveBlocks), 64, 0, s>>>(a, td, tab, pos, ph, cnt, fb_list, fb_count, rl, list,
+                                                             gcount, counts, fb2_list, fb2_count, nullptr, !direct);
+    k_solve_h_fallback<<<std::min(a.n, kFallbackWaves), 64, 0, s>>>(a, td, tab, pos, ph, cnt, fb2_list, fb2_count, list,
+                                                                    gcount, counts, nullptr);
     if (t1) hipEventRecord(t1, s);
 }
 
@@ -1962,14 +2014,20 @@ void launch_solve_h_active(const PassArrays& a, const TreeDesc& td, const int2* 
                            int* fb2_list, unsigned long long* fb2_count, hipStream_t s) {
     launch_fill_u64(1, fb_count, 0ull, s);
     launch_fill_u64(1, fb2_count, 0ull, s);
-    k_solve_h<true><<<blocks_of(a.n, 256), 256, 0, s>>>(a, td, tab, pos, keys, ph, cnt, rl, list, gcount, counts,
-                                                        fb_list, fb_count, mode, pad);
-    k_root_h<true><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph.n_ngb, ph.h_maxit, cnt, rl, list, gcount, counts, fb_list,
-                                                       fb_count, mode);
-    k_solve_h_wave<<<kWaveBlocks, 64, 0, s>>>(a, td, tab, pos, ph, cnt, fb_list, fb_count, rl, list, gcount,
-                                              counts, fb2_list, fb2_count, pad);
-    k_solve_h_fallback<<<kFallbackWaves, 64, 0, s>>>(a, td, tab, pos, ph, cnt, fb2_list, fb2_count, list, gcount,
-                                                     counts, pad);
+    const bool direct = a.n <= kDirectMax;
+    if (direct) {
+        k_solve_start<true><<<blocks_of(a.n, 256), 256, 0, s>>>(a, td, tab, keys, ph, rl, fb_list, fb_count, fb2_count,
+                                                                mode);
+    } else {
+        k_solve_h<true><<<blocks_of(a.n, 256), 256, 0, s>>>(a, td, tab, pos, keys, ph, cnt, rl, list, gcount, counts,
+                                                            fb_list, fb_count, mode, pad);
+        k_root_h<true><<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph.n_ngb, ph.h_maxit, cnt, rl, list, gcount, counts,
+                                                           fb_list, fb_count, mode);
+    }
+    k_solve_h_wave<<<std::min(a.n, kWaveBlocks), 64, 0, s>>>(a, td, tab, pos, ph, cnt, fb_list, fb_count, rl, list,
+                                                             gcount, counts, fb2_list, fb2_count, pad, !direct);
+    k_solve_h_fallback<<<std::min(a.n, kFallbackWaves), 64, 0, s>>>(a, td, tab, pos, ph, cnt, fb2_list, fb2_count, list,
+                                                                    gcount, counts, pad);
     k_gather_kept<<<blocks_of(a.n, 256), 256, 0, s>>>(a, td, tab, pos, ph, mode, pad, list, gcount, counts);
 }
 

@@ -38,7 +38,10 @@ def _set(kind, n, seed):
 # n_ngb 55 and 100: about 64 and 120 radii a particle, up to and past what the root kernel keeps in registers
 @pytest.mark.parametrize("kind,n,n_ngb", [("uniform", 300, 32.0), ("uniform", 70001, 32.0), ("slab", 66000, 32.0),
                                           ("clumps", 2500, 32.0), ("clumps", 70003, 32.0), ("slab", 40009, 55.0),
-                                          ("uniform", 40009, 100.0)])
+                                          ("uniform", 40009, 100.0),
+                                          # the last size solved one wave a particle, the first of the group scan
+                                          ("uniform", 49152, 32.0), ("uniform", 49153, 32.0), ("clumps", 49152, 32.0),
+                                          ("clumps", 49153, 32.0), ("slab", 50001, 55.0), ("uniform", 50001, 100.0)])
 def test_lists_and_kernel_lengths_equal_brute_force(kind, n, n_ngb):
     import dataclasses
 
