@@ -221,6 +221,44 @@ __device__ __forceinline__ T wave_reduce(T v, Op op) {
     return op(a.value(), b.value());
 }
 
+// op over the SPLIT lanes that share a particle: lanes 64 / SPLIT apart (SPLIT
+// 1, 2, 4 or 8), the same order on each
+template <int SPLIT, typename T, typename Op>
+__device__ __forceinline__ T split_reduce(T v, Op op) {
+    using W = Words<T>;
+    if constexpr (SPLIT >= 2) {
+        W a = W::of(v), b = a;
+#pragma unroll
+        for (int k = 0; k < W::n; k++) swap_halves(a.w[k], b.w[k]);
+        v = op(a.value(), b.value());
+    }
+    if constexpr (SPLIT >= 4) {
+        W a = W::of(v), b = a;
+#pragma unroll
+        for (int k = 0; k < W::n; k++) swap_rows(a.w[k], b.w[k]);
+        v = op(a.value(), b.value());
+    }
+    if constexpr (SPLIT >= 8) {
+        W b = W::of(v);
+#pragma unroll
+        for (int k = 0; k < W::n; k++) b.w[k] = lane_move<0x128>(b.w[k]);   // row rotated by 8
+        v = op(v, b.value());
+    }
+    return v;
+}
+template <int SPLIT>
+__device__ __forceinline__ void split_sum(double& v) {
+    v = split_reduce<SPLIT>(v, [](double a, double b) { return a + b; });
+}
+template <int SPLIT>
+__device__ __forceinline__ void split_max(double& v) {
+    v = split_reduce<SPLIT>(v, [](double a, double b) { return fmax(a, b); });
+}
+template <int SPLIT>
+__device__ __forceinline__ void split_min(double& v) {
+    v = split_reduce<SPLIT>(v, [](double a, double b) { return fmin(a, b); });
+}
+
 // the sums of u and v at once, each in the order of a sum of its own: after the
 // first step the lower half of the wave carries u and the upper half v
 __device__ __forceinline__ void wave_sum2_d(double u, double v, double& su, double& sv) {

@@ -1,6 +1,6 @@
 // The gfx950 MFM hydro pass: kernel length, flux lists, gradients, fluxes.
 //
-// One thread per (Morton-ordered) particle; blocks are remapped so that each
+// One thread, or a few that share its list, per (Morton-ordered) particle; blocks are remapped so that each
 // XCD works on one contiguous run of particles and keeps its neighbours in
 // its own L2.  The flux kernel evaluates every unordered pair on both of its
 // particles with the lower index as the left state, so both copies are
@@ -1073,8 +1073,7 @@ __global__ void k_pack_prim_active(PassArrays a, Phys ph, const int* __restrict_
     for (int k = 0; k < cnum; k++) pack_one(a, ph, prim, list[(long long)k * n + i]);
 }
 
-// One thread per particle, one wave per block; the neighbours' records come by
-// lane teams, and while one is summed the next is on its way to LDS.  The tail
+// One wave per block; the neighbours' records come by lane teams, and while one is summed the next is on its way to LDS.  The tail
 // appends of the wave queue in LDS until the sums are done: in the loop a wave
 // had an atomic's round trip to L2 in nearly every step.  Then the queue is
 // worked off 64 at a time, four rounds in flight; the entries of a round that go
@@ -1087,6 +1086,17 @@ __global__ void k_pack_prim_active(PassArrays a, Phys ph, const int* __restrict_
 // With HIER (hierarchical steps with active subsets) only the particles of
 // mode kModeSolve get new gradients; a kept particle with a gather list only
 // appends itself to the lists of its active neighbours that do not reach it.
+// A particle's list is shared by SPLIT lanes, 64 / SPLIT apart, whose sums meet
+// at the end: with one lane a particle, a set of 32,768 is 512 waves for 1,024
+// SIMDs, each as long as its longest list.  Up to kGradSplit4 particles four
+// lanes, up to kGradSplit2 two; beyond, where the waves fill the chip, one
+// (the sums of E stay in the order of the list, which the gradient matrices of
+// ill-conditioned particles show).  Measured, one / two / four / eight lanes:
+// lattice 4,096 36 / 23 / 18 / 18 us, 32,768 39 / 31 / 29 / 39, 64,000 48 / 38 /
+// 42 / 52, 110,592 53 / 54 / 57 / 78; clustered 32,768 182 / 92 / 54 / 51,
+// 64,000 293 / 117 / 73 / 63, 110,592 158 / 95 / 79 / 86.
+constexpr int kGradSplit4 = 65536;
+constexpr int kGradSplit2 = 131072;
 constexpr int kGradWaves = 3;
 constexpr int kAppends = 768;   // appends a wave holds back
 struct GradLds {
@@ -1094,7 +1104,7 @@ struct GradLds {
     int to[kAppends];               // particle j whose list takes ...
     unsigned char from[kAppends];   // ... the particle of this lane
 };
-template <bool MIXED, bool HIER>
+template <bool MIXED, bool HIER, int SPLIT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))) void k_gradients(PassArrays a, Phys ph, const int* __restrict__ gcount,
                                                     int* __restrict__ counts, int* __restrict__ list, Bins bins,
                                                     const double4* __restrict__ prim, void* __restrict__ recp,
@@ -1103,8 +1113,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
     cnt = counter_copy(cnt);
     __shared__ GradLds lds;
     TeamLds<8>& S8 = lds.t;
-    const int lane = threadIdx.x;
-    const int i = xcd_block() * kWave + lane;
+    static_assert(!HIER || SPLIT == 1, "one lane per particle with active subsets");
+    constexpr int kOwn = kWave / SPLIT;   // particles of the wave
+    const int lane = threadIdx.x, sub = lane / kOwn;
+    const int i = xcd_block() * kOwn + lane % kOwn;
     if (HIER && i < a.n && mode[i] == kModeKept) {
         const long long n = a.n;
         const double xi[3] = {a.x[i], a.y[i], a.z[i]};
@@ -1151,8 +1163,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
     const float normf = (float)norm, iHf = (float)iH;
     const int cap = ph.max_ngb;
     const int self = i < a.n ? i : a.n - 1;   // a record to load where a lane has no neighbour
-    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i(cnum));
-    auto entry = [&](int k) { return k < cnum ? list[(long long)k * n + i] : -1; };
+    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i((cnum + SPLIT - 1) / SPLIT));
+    auto entry = [&](int k) {
+        const int e = k * SPLIT + sub;
+        return e < cnum ? list[(long long)e * n + i] : -1;
+    };
     int j = entry(0), jn = entry(1);
     int napp = 0;   // appends of the wave so far
     const unsigned long long below = (1ull << lane) - 1ull;
@@ -1214,7 +1229,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
         rmax = fmax(rmax, r);
     }
     {
-        const int held = min(napp, kAppends), r0 = i - lane;
+        const int held = min(napp, kAppends), r0 = i - lane % kOwn;
         wave_lds_sync();
         for (int b = 0; b < held; b += 4 * kWave) {
             int to[4], lead[4], rank[4], at[4];
@@ -1245,10 +1260,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
                 const int base = __shfl(at[q], lead[q], kWave);
                 if (to[q] >= 0)
                     bin_store(bins, counts, list, gcount, cap, a.n, to[q], base + rank[q],
-                              r0 + lds.from[b + q * kWave + lane]);
+                              r0 + lds.from[b + q * kWave + lane] % kOwn);
             }
         }
     }
+#pragma unroll
+    for (int k = 0; k < 6; k++) split_sum<SPLIT>(E[k]);
+#pragma unroll
+    for (int k = 0; k < 15; k++) split_sum<SPLIT>(S[k]);
+#pragma unroll
+    for (int f = 0; f < 5; f++) {
+        split_max<SPLIT>(pmax[f]);
+        split_min<SPLIT>(pmin[f]);
+    }
+    split_max<SPLIT>(rmax);
+    const bool own = act && sub == 0;
     // (lanes without a particle run along on zeros and store nothing)
     {
         // B = E^-1 by cofactors (E symmetric: xx xy xz yy yz zz)
@@ -1264,11 +1290,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
         const double fe = E[0] * E[0] + E[3] * E[3] + E[5] * E[5] + 2.0 * (E[1] * E[1] + E[2] * E[2] + E[4] * E[4]);
         const double fb = B[0] * B[0] + B[3] * B[3] + B[5] * B[5] + 2.0 * (B[1] * B[1] + B[2] * B[2] + B[4] * B[4]);
         const double cond = sqrt(fe) * sqrt(fb);
-        if (act && (!(det > 0.0) || !(cond <= ph.cond_max))) {
+        if (own && (!(det > 0.0) || !(cond <= ph.cond_max))) {
             ill = 1;
             flag_index(cnt, i);
         }
-        if (act && cond > 0.0) condbits = __double_as_longlong(cond);
+        if (own && cond > 0.0) condbits = __double_as_longlong(cond);
         // the limiter constant: beta, or with the optional limiters (R24) beta moved
         // towards beta_min linearly in log10(cond) between cond_lo and cond_hi
         double beta = ph.beta;
@@ -1314,7 +1340,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
             g[3 * f + 1] = alpha * g1;
             g[3 * f + 2] = alpha * g2;
         }
-        if (act) {
+        if (own) {
             const long long io = HIER ? home[i] : i;   // column of B, grad and alpha
 #pragma unroll
             for (int k = 0; k < 6; k++) a.B[k * n + io] = B[k];
@@ -1358,7 +1384,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
         v[R_C] = (T)c_i;
         // the wave's records, 128 bytes of each at a time, transposed in LDS: eight
         // lanes then store one record's line
-        const unsigned long long stored = __ballot(act);
+        const unsigned long long stored = __ballot(own);
 #pragma unroll
         for (int h = 0; h < (int)sizeof(T) / 4; h++) {
             wave_lds_sync();
@@ -1369,7 +1395,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kGradWaves))
                 team_put(S8, c, lane, u);
             }
             wave_lds_sync();
-            team_store<32 * sizeof(T)>(S8, (char*)recp + (size_t)(unsigned)(i - lane) * (32 * sizeof(T)) + 128 * h,
+            team_store<32 * sizeof(T)>(S8, (char*)recp + (size_t)(unsigned)(i - lane % kOwn) * (32 * sizeof(T)) + 128 * h,
                                        stored, lane);
         }
     }
@@ -1730,15 +1756,17 @@ struct FluxLds<float> {
     TeamLds<2> pos;
 };
 
-template <typename T, bool MFV, bool LIM, bool LEV = false>
+template <typename T, bool MFV, bool LIM, int SPLIT, bool LEV = false>
 __device__ __forceinline__ void fluxes_body(const PassArrays& a, const Phys& ph, const int* __restrict__ counts,
                                             const int* __restrict__ list, const T* __restrict__ rec,
                                             const double4* __restrict__ prim, Counters* cnt,
                                             Levels lv = Levels{nullptr, 0, 0, nullptr, nullptr}) {
     cnt = counter_copy(cnt);
     __shared__ FluxLds<T> S;
-    const int lane = threadIdx.x;
-    const int i = xcd_block() * kWave + lane;
+    static_assert(!LEV || SPLIT == 1, "the levelled sums are one lane's");
+    constexpr int kOwn = kWave / SPLIT;   // particles of the wave
+    const int lane = threadIdx.x, sub = lane / kOwn;
+    const int i = xcd_block() * kOwn + lane % kOwn;
     const bool act = i < a.n;
     const long long n = a.n;
     const int self = act ? i : a.n - 1;   // a record to load where a lane has no pair
@@ -1787,8 +1815,11 @@ __device__ __forceinline__ void fluxes_body(const PassArrays& a, const Phys& ph,
     // levelled pass costs its bin alone (no flux, no signal speed: the last
     // boundary of a system step has every pair due, so the signal speeds it
     // leaves are complete), and a step without a due pair loads no records.
-    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i(cnum));
-    auto entry = [&](int k) { return k < cnum ? list[(long long)k * n + i] : -1; };
+    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i((cnum + SPLIT - 1) / SPLIT));
+    auto entry = [&](int k) {
+        const int e = k * SPLIT + sub;
+        return e < cnum ? list[(long long)e * n + i] : -1;
+    };
     auto level = [&](int j) { return j >= 0 ? max(bi, (int)lv.bin[j]) : -1; };
     auto is_due = [&](int j, int l) { return j >= 0 && (!LEV || l >= lv.lmin); };
     auto start = [&](bool on, int j) {
@@ -1877,7 +1908,11 @@ __device__ __forceinline__ void fluxes_body(const PassArrays& a, const Phys& ph,
             }
         }
     }
-    if (act) {
+#pragma unroll
+    for (int c = 0; c < 4; c++) split_sum<SPLIT>(acc[c]);
+    if (MFV) split_sum<SPLIT>(accm);
+    split_max<SPLIT>(vs);
+    if (act && sub == 0) {
         if (LEV) {
 #pragma unroll
             for (int w = 0; w < kLevWin; w++) {
@@ -1918,13 +1953,21 @@ __device__ __forceinline__ void fluxes_body(const PassArrays& a, const Phys& ph,
 // 32-bit record offsets and the square roots with their reciprocals); mixed MFM,
 // shock tube 295k 0.232 -> 0.181 ms; limited FP64, clustered 2.1M 4.35 -> 3.47
 // ms; levelled, hierarchical step of 2.1M 0.89 -> 0.69 ms a launch.
+// A particle's list is shared by SPLIT lanes: eight up to kFluxSplit8 particles
+// (too few waves for the chip otherwise), two beyond (a wave of 32 particles
+// waits for the longest of 32 lists, not of 64); the levelled form keeps one.
+// Measured, one / two / four / eight lanes: lattice 4,096 52 / 29 / 18 / 13 us,
+// 32,768 54 / 34 / 30 / 33, 64,000 59 / 48 / 49 / 54, 2.1M 1.10 / 1.09 / 1.14 ms;
+// clustered 32,768 201 / 107 / 63 / 52 us, 64,000 329 / 168 / 104 / 80, 16.8M
+// 13.9 / 12.6 / 12.2 ms; mixed, shock tube 295k 0.189 / 0.145 / 0.141 ms.
+constexpr int kFluxSplit8 = 49152;
 constexpr int kFlux64Waves = 2;
 constexpr int kFluxMfvWaves = kFlux64Waves;
-template <bool LIM>
+template <bool LIM, int SPLIT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFlux64Waves))) void k_fluxes_f64(PassArrays a, Phys ph, const int* __restrict__ counts,
                                                     const int* __restrict__ list, const double* __restrict__ rec,
                                                     const double4* __restrict__ prim, Counters* cnt) {
-    fluxes_body<double, false, LIM>(a, ph, counts, list, rec, prim, cnt);
+    fluxes_body<double, false, LIM, SPLIT>(a, ph, counts, list, rec, prim, cnt);
 }
 
 // The levelled pass of hierarchical steps (MFM, FP64 records).
@@ -1932,32 +1975,32 @@ template <bool LIM>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFlux64Waves))) void k_fluxes_levels(
     PassArrays a, Phys ph, const int* __restrict__ counts, const int* __restrict__ list,
     const double* __restrict__ rec, const double4* __restrict__ prim, Counters* cnt, Levels lv) {
-    fluxes_body<double, false, LIM, true>(a, ph, counts, list, rec, prim, cnt, lv);
+    fluxes_body<double, false, LIM, 1, true>(a, ph, counts, list, rec, prim, cnt, lv);
 }
 
 // The finite-volume form, FP64 records only, at two waves per SIMD like the
 // FP64 form (at three its extra live values spill).
-template <bool LIM>
+template <bool LIM, int SPLIT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFluxMfvWaves))) void k_fluxes_mfv(PassArrays a, Phys ph, const int* __restrict__ counts,
                                                     const int* __restrict__ list, const double* __restrict__ rec,
                                                     const double4* __restrict__ prim, Counters* cnt) {
-    fluxes_body<double, true, LIM>(a, ph, counts, list, rec, prim, cnt);
+    fluxes_body<double, true, LIM, SPLIT>(a, ph, counts, list, rec, prim, cnt);
 }
 
 constexpr int kFlux32Waves = 3;
-template <bool LIM>
+template <bool LIM, int SPLIT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFlux32Waves)))
 void k_fluxes_f32(PassArrays a, Phys ph, const int* __restrict__ counts, const int* __restrict__ list,
                   const float* __restrict__ rec, const double4* __restrict__ prim, Counters* cnt) {
-    fluxes_body<float, false, LIM>(a, ph, counts, list, rec, prim, cnt);
+    fluxes_body<float, false, LIM, SPLIT>(a, ph, counts, list, rec, prim, cnt);
 }
 
 // The finite-volume form on the FP32 records of the mixed form.
-template <bool LIM>
+template <bool LIM, int SPLIT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFlux32Waves)))
 void k_fluxes_mfv_f32(PassArrays a, Phys ph, const int* __restrict__ counts, const int* __restrict__ list,
                       const float* __restrict__ rec, const double4* __restrict__ prim, Counters* cnt) {
-    fluxes_body<float, true, LIM>(a, ph, counts, list, rec, prim, cnt);
+    fluxes_body<float, true, LIM, SPLIT>(a, ph, counts, list, rec, prim, cnt);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -1992,18 +2035,30 @@ void launch_solve_h(const PassArrays& a, const TreeDesc& td, const int2* tab,
     if (t1) hipEventRecord(t1, s);
 }
 
+template <int SPLIT>
+static void launch_gradients_split(const PassArrays& a, const Phys& ph, const int* gcount, int* counts, int* list,
+                                   const Bins& bins, int mixed, double4* prim, void* rec, Counters* cnt, hipStream_t s) {
+    const int blocks = blocks_of(a.n, kWave / SPLIT);
+    if (mixed)
+        k_gradients<true, false, SPLIT><<<blocks, kWave, 0, s>>>(a, ph, gcount, counts, list, bins, prim, rec, cnt,
+                                                                 nullptr, nullptr);
+    else
+        k_gradients<false, false, SPLIT><<<blocks, kWave, 0, s>>>(a, ph, gcount, counts, list, bins, prim, rec, cnt,
+                                                                  nullptr, nullptr);
+}
+
 void launch_gradients(const PassArrays& a, const Phys& ph, const int* gcount, int* counts, int* list, int2* bin_entry, int* bin_fill,
                       int mixed, double4* prim, void* rec, Counters* cnt, hipEvent_t t0, hipEvent_t t1,
                       hipStream_t s) {
     const Bins bins{bin_entry, bin_fill};
     k_pack_prim<<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, prim, bin_fill);
     if (t0) hipEventRecord(t0, s);
-    if (mixed)
-        k_gradients<true, false><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, gcount, counts, list, bins, prim, rec,
-                                                                     cnt, nullptr, nullptr);
+    if (a.n <= kGradSplit4)
+        launch_gradients_split<4>(a, ph, gcount, counts, list, bins, mixed, prim, rec, cnt, s);
+    else if (a.n <= kGradSplit2)
+        launch_gradients_split<2>(a, ph, gcount, counts, list, bins, mixed, prim, rec, cnt, s);
     else
-        k_gradients<false, false><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, gcount, counts, list, bins, prim, rec,
-                                                                      cnt, nullptr, nullptr);
+        launch_gradients_split<1>(a, ph, gcount, counts, list, bins, mixed, prim, rec, cnt, s);
     if (t1) hipEventRecord(t1, s);
     k_sort_tails<<<blocks_of(a.n, 256), 256, 0, s>>>(a.n, ph.max_ngb, gcount, counts, list, bins, cnt);
 }
@@ -2036,23 +2091,33 @@ void launch_gradients_active(const PassArrays& a, const Phys& ph, const unsigned
                              Counters* cnt, hipStream_t s) {
     const Bins bins{bin_entry, bin_fill};
     k_pack_prim_active<<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, gcount, mode, list, prim, bin_fill);
-    k_gradients<false, true><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, gcount, counts, list, bins, prim, rec, cnt,
+    k_gradients<false, true, 1><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, gcount, counts, list, bins, prim, rec, cnt,
                                                                  mode, home);
     k_sort_tails<<<blocks_of(a.n, 256), 256, 0, s>>>(a.n, ph.max_ngb, gcount, counts, list, bins, cnt);
     k_pack_rec_kept<<<blocks_of(a.n, 256), 256, 0, s>>>(a, ph, mode, home, counts, (double*)rec);
 }
 
+template <bool LIM, int SPLIT>
+static void launch_fluxes_split(const PassArrays& a, const Phys& ph, const int* counts, const int* list, int mixed,
+                                int mfv, const void* rec, const double4* prim, Counters* cnt, hipStream_t s) {
+    const int blocks = blocks_of(a.n, kWave / SPLIT);
+    if (mfv && mixed)
+        k_fluxes_mfv_f32<LIM, SPLIT><<<blocks, kWave, 0, s>>>(a, ph, counts, list, (const float*)rec, prim, cnt);
+    else if (mfv)
+        k_fluxes_mfv<LIM, SPLIT><<<blocks, kWave, 0, s>>>(a, ph, counts, list, (const double*)rec, prim, cnt);
+    else if (mixed)
+        k_fluxes_f32<LIM, SPLIT><<<blocks, kWave, 0, s>>>(a, ph, counts, list, (const float*)rec, prim, cnt);
+    else
+        k_fluxes_f64<LIM, SPLIT><<<blocks, kWave, 0, s>>>(a, ph, counts, list, (const double*)rec, prim, cnt);
+}
+
 template <bool LIM>
 static void launch_fluxes_lim(const PassArrays& a, const Phys& ph, const int* counts, const int* list, int mixed,
                               int mfv, const void* rec, const double4* prim, Counters* cnt, hipStream_t s) {
-    if (mfv && mixed)
-        k_fluxes_mfv_f32<LIM><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, counts, list, (const float*)rec, prim, cnt);
-    else if (mfv)
-        k_fluxes_mfv<LIM><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, counts, list, (const double*)rec, prim, cnt);
-    else if (mixed)
-        k_fluxes_f32<LIM><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, counts, list, (const float*)rec, prim, cnt);
+    if (a.n <= kFluxSplit8)
+        launch_fluxes_split<LIM, 8>(a, ph, counts, list, mixed, mfv, rec, prim, cnt, s);
     else
-        k_fluxes_f64<LIM><<<blocks_of(a.n, kWave), kWave, 0, s>>>(a, ph, counts, list, (const double*)rec, prim, cnt);
+        launch_fluxes_split<LIM, 2>(a, ph, counts, list, mixed, mfv, rec, prim, cnt, s);
 }
 
 void launch_fluxes_levels(const PassArrays& a, const Phys& ph, const int* counts, const int* list, const void* rec,

@@ -108,3 +108,30 @@ def test_pass_at_the_edges_of_a_wave(n, precision):
             assert e <= 1e-12, (k, e)
         elif k in ("dp", "dE"):
             assert e <= 1e-5, (k, e)
+
+
+@pytest.mark.parametrize("precision", [0, 1], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("n", [49152, 49153, 65536, 65537, 131072, 131073])
+def test_pass_on_both_sides_of_the_lane_split(n, precision):
+    """The sizes at which the number of lanes that share a particle's list
+    changes in the gradients and the fluxes: the first, some middle and the last
+    particles (the last, partly filled wave) of a random open set, against the
+    oracle on the same sample (the bars of the full passes)."""
+    from .gpu_util import in_input_order, nerr, oracle_sample, run_pass
+    rng = np.random.default_rng(W.SEED_BASE + 780)
+    w = W.Workload(name="split", x=rng.uniform(0, 1, n), y=rng.uniform(0, 1, n), z=rng.uniform(0, 1, n),
+                   m=rng.uniform(0.5, 1.5, n) / n, vx=rng.normal(0, 0.2, n), vy=rng.normal(0, 0.2, n),
+                   vz=rng.normal(0, 0.2, n), u=rng.uniform(1, 2, n), gamma=1.4, box=(1.0, 1.0, 1.0),
+                   periodic=(1, 1, 1))
+    ctx, st = run_pass(w, precision=precision)
+    ctx.check(allow_illcond=True)
+    ids = st.id.cpu().numpy()
+    targets = np.concatenate([ids[:8], ids[n // 2:n // 2 + 8], ids[-16:]])
+    ref = oracle_sample(w, targets)
+    # E^-1 amplifies the rounding of the sums of E by cond(E)
+    tol = max(1e-12, 32 * np.finfo(np.float64).eps * float(ref["cond"][targets].max()))
+    for k in ("H", "nk", "rho", "P", "dp", "dE") + (() if precision else ("B", "grad", "vsig")):
+        e = nerr(in_input_order(st, k)[..., targets], ref[k][..., targets])
+        print(n, precision, k, f"{e:.1e}", flush=True)
+        bar = 1e-12 if k not in ("B", "grad", "dp", "dE") else 1e-5 if precision else tol
+        assert e <= bar, (k, e)
