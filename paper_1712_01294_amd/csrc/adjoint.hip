@@ -358,11 +358,13 @@ struct AdjPairLds {
     TeamLds<16> own, other;
     TeamLds<2> lam;
 };
+template <int SPLIT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kAdjPairWaves))) void k_adj_pairs(PassArrays a, Phys ph, const int* __restrict__ counts,
                                                     const int* __restrict__ list, AdjRecords ar, AdjArrays aj) {
     __shared__ AdjPairLds S;
-    const int lane = threadIdx.x;
-    const int i = xcd_block_adj() * kWave + lane;
+    constexpr int kOwn = kWave / SPLIT;   // particles of the wave
+    const int lane = threadIdx.x, sub = lane / kOwn;
+    const int i = xcd_block_adj() * kOwn + lane % kOwn;
     const bool act = i < a.n;
     const long long n = a.n;
     const int self = act ? i : a.n - 1;
@@ -370,8 +372,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kAdjPairWave
     zero_adj(own);
     double lx[3] = {0.0, 0.0, 0.0};
     const int cnum = act ? counts[i] : 0;
-    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i(cnum));
-    auto entry = [&](int k) { return k < cnum ? list[(long long)k * n + i] : -1; };
+    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i((cnum + SPLIT - 1) / SPLIT));
+    auto entry = [&](int k) {
+        const int e = k * SPLIT + sub;
+        return e < cnum ? list[(long long)e * n + i] : -1;
+    };
     auto start = [&](int j) {
         const int jr = j >= 0 ? j : self;
         team_load<8 * kAdjRec, 16>(S.other, ar.rec, a.n, jr, lane);
@@ -422,7 +427,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kAdjPairWave
         const double sg = iL ? -1.0 : 1.0;
         for (int c = 0; c < 3; c++) lx[c] += sg * ld[c];
     }
-    if (!act) return;
+    for (int c = 0; c < 3; c++) split_sum<SPLIT>(lx[c]);
+    for (int f = 0; f < 5; f++) split_sum<SPLIT>(own.phi[f]);
+    split_sum<SPLIT>(own.H);
+    split_sum<SPLIT>(own.V);
+    for (int k = 0; k < 6; k++) split_sum<SPLIT>(own.B[k]);
+    for (int k = 0; k < 15; k++) split_sum<SPLIT>(own.g[k]);
+    if (!act || sub != 0) return;
     for (int c = 0; c < 3; c++) aj.acc_x[c * n + i] = lx[c];
     for (int f = 0; f < 5; f++) aj.acc_phi[f * n + i] = own.phi[f];
     aj.acc_H[i] = own.H;
@@ -502,39 +513,46 @@ __device__ __forceinline__ void grad_pair_terms(const double d[3], double r, dou
     lpsi_out = lpsi;
 }
 
+// an extremum and the entry of the gather list that holds it
+struct Peak {
+    double v;
+    int e, z;
+};
+
 // (a block is one wave; the LDS of its gathers takes the records out as well)
+template <int SPLIT>
 __global__ __launch_bounds__(64) void k_adj_grad_own(PassArrays a, Phys ph, const int* __restrict__ gcount,
                                                       const int* __restrict__ list, AdjRecords ar, AdjArrays aj,
                                                       PullArrays pa) {
     __shared__ TeamLds<16> S16;
     TeamLds<8>& S8 = *(TeamLds<8>*)&S16;
-    const int lane = threadIdx.x;
-    const int i_ = xcd_block_adj() * kWave + lane;
+    constexpr int kOwn = kWave / SPLIT;   // particles of the wave
+    const int lane = threadIdx.x, sub = lane / kOwn;
+    const int i_ = xcd_block_adj() * kOwn + lane % kOwn;
     const bool act = i_ < a.n;
     const int i = act ? i_ : a.n - 1;   // lanes without a particle run along on the last one and store nothing
-    const unsigned long long lanes = __ballot(act);
+    const unsigned long long lanes = __ballot(act && sub == 0);
     const long long n = a.n;
     const double xi[3] = {a.x[i], a.y[i], a.z[i]};
     const double Hi = a.H[i], Vi = a.V[i];
     const double rho_i = a.m[i] * a.nk[i];
     const double phi_i[5] = {rho_i, a.vx[i], a.vy[i], a.vz[i], (ph.gamma - 1.0) * rho_i * a.u[i]};
     const int cnum = act ? gcount[i] : 0;
-    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i(cnum));
-    auto entry = [&](int k) { return k < cnum ? list[(long long)k * n + i] : -1; };
+    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i((cnum + SPLIT - 1) / SPLIT));
+    auto entry = [&](int k) {
+        const int e = k * SPLIT + sub;
+        return e < cnum ? list[(long long)e * n + i] : -1;
+    };
     // recompute the forward sums, extrema and their owners
     double E[6] = {0, 0, 0, 0, 0, 0}, S[15];
     for (int k = 0; k < 15; k++) S[k] = 0.0;
-    double pmax[5], pmin[5];
-    int jmax[5], jmin[5];
-    for (int f = 0; f < 5; f++) {
-        pmax[f] = pmin[f] = phi_i[f];
-        jmax[f] = jmin[f] = i;
-    }
-    double rmax = 0.0, sqdw = 0.0;   // sqdw: sum of q w'(q), for the kernel-length reverse
+    // (with the list entry that holds each, -1 the particle itself; the first of equals)
+    Peak pmax[5], pmin[5], far = {0.0, -1, 0};
+    for (int f = 0; f < 5; f++) pmax[f] = pmin[f] = Peak{phi_i[f], -1, 0};
+    double sqdw = 0.0;   // sqdw: sum of q w'(q), for the kernel-length reverse
     const double iH = 1.0 / Hi, nrm = kernel_norm(Hi);
-    int jr = i;
     // one neighbour per lane and step, the next one's record on its way to LDS and
-    // the index of the one after to a register; body(j, x (3), rho, v (3), P)
+    // the index of the one after to a register; body(entry, x (3), rho, v (3), P)
     auto walk = [&](auto&& body) {
         int j = entry(0), jn = entry(1);
         if (kmax > 0) team_load<8 * kAdjNgb, 5>(S8, ar.ngb, a.n, j >= 0 ? j : i, lane);
@@ -549,10 +567,10 @@ __global__ __launch_bounds__(64) void k_adj_grad_own(PassArrays a, Phys ph, cons
             wait_lds();
             if (k + 1 < kmax) team_load<8 * kAdjNgb, 5>(S8, ar.ngb, a.n, j >= 0 ? j : i, lane);
             jn = entry(k + 2);
-            if (jc >= 0) body(jc, rc);
+            if (jc >= 0) body(k * SPLIT + sub, rc);
         }
     };
-    walk([&](int j, const double* rc) {
+    walk([&](int e, const double* rc) {
         double d[3];
         disp(ph, xi, rc[0], rc[1], rc[2], d);
         const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
@@ -571,20 +589,26 @@ __global__ __launch_bounds__(64) void k_adj_grad_own(PassArrays a, Phys ph, cons
             S[3 * f] += df * d[0];
             S[3 * f + 1] += df * d[1];
             S[3 * f + 2] += df * d[2];
-            if (phi_j[f] > pmax[f]) {
-                pmax[f] = phi_j[f];
-                jmax[f] = j;
-            }
-            if (phi_j[f] < pmin[f]) {
-                pmin[f] = phi_j[f];
-                jmin[f] = j;
-            }
+            if (phi_j[f] > pmax[f].v) pmax[f] = Peak{phi_j[f], e, 0};
+            if (phi_j[f] < pmin[f].v) pmin[f] = Peak{phi_j[f], e, 0};
         }
-        if (r > rmax) {
-            rmax = r;
-            jr = j;
-        }
+        if (r > far.v) far = Peak{r, e, 0};
     });
+    for (int k = 0; k < 6; k++) split_sum<SPLIT>(E[k]);
+    for (int k = 0; k < 15; k++) split_sum<SPLIT>(S[k]);
+    split_sum<SPLIT>(sqdw);
+    for (int f = 0; f < 5; f++) {
+        pmax[f] = split_reduce<SPLIT>(pmax[f], [](const Peak& p, const Peak& q) {
+            return p.v > q.v || (p.v == q.v && p.e < q.e) ? p : q;
+        });
+        pmin[f] = split_reduce<SPLIT>(pmin[f], [](const Peak& p, const Peak& q) {
+            return p.v < q.v || (p.v == q.v && p.e < q.e) ? p : q;
+        });
+    }
+    far = split_reduce<SPLIT>(far, [](const Peak& p, const Peak& q) {
+        return p.v > q.v || (p.v == q.v && p.e < q.e) ? p : q;
+    });
+    auto holder = [&](const Peak& p) { return p.e >= 0 ? list[(long long)p.e * n + i] : i; };
     const double c00 = E[3] * E[5] - E[4] * E[4];
     const double c01 = E[2] * E[4] - E[1] * E[5];
     const double c02 = E[1] * E[4] - E[2] * E[3];
@@ -595,7 +619,7 @@ __global__ __launch_bounds__(64) void k_adj_grad_own(PassArrays a, Phys ph, cons
     const double id = 1.0 / det;
     const double B[6] = {c00 * id, c01 * id, c02 * id, c11 * id, c12 * id, c22 * id};
     const double Bf[3][3] = {{B[0], B[1], B[2]}, {B[1], B[3], B[4]}, {B[2], B[4], B[5]}};
-    const double half = 0.5 * rmax;
+    const double half = 0.5 * far.v;
     // Lambda: full 3x3 adjoint of B; the stored-component adjoint of an
     // off-diagonal entry is split evenly between its two positions
     double Lam[3][3];
@@ -620,8 +644,8 @@ __global__ __launch_bounds__(64) void k_adj_grad_own(PassArrays a, Phys ph, cons
         const double gn = sqrt(g[0] * g[0] + g[1] * g[1] + g[2] * g[2]);
         double alpha = 1.0, up = 0.0, dn = 0.0;
         if (gn > 0.0) {
-            up = (pmax[f] - phi_i[f]) / (gn * half);
-            dn = (phi_i[f] - pmin[f]) / (gn * half);
+            up = (pmax[f].v - phi_i[f]) / (gn * half);
+            dn = (phi_i[f] - pmin[f].v) / (gn * half);
             alpha = fmin(1.0, ph.beta * fmin(up, dn));
         }
         double lg[3];
@@ -677,13 +701,15 @@ __global__ __launch_bounds__(64) void k_adj_grad_own(PassArrays a, Phys ph, cons
         wave_lds_sync();
         put_pairs(S16, v, 32, lane);
         wave_lds_sync();
-        team_store<8 * kAdjRec>(S16, pa.rec + (long long)(i_ - lane) * kAdjRec, lanes, lane);
+        team_store<8 * kAdjRec>(S16, pa.rec + (long long)(i_ - lane % kOwn) * kAdjRec, lanes, lane);
         wave_lds_sync();
     }
     // i's side of every pair of its gather set
     double lH = 0.0, lV = 0.0;
     double lxi[3] = {0.0, 0.0, 0.0};
-    walk([&](int j, const double* rc) {
+    if (sub != 0)
+        for (int f = 0; f < 5; f++) lphi_i[f] = 0.0;   // (the limiter's terms enter one lane's sums)
+    walk([&](int e, const double* rc) {
         double d[3];
         disp(ph, xi, rc[0], rc[1], rc[2], d);
         const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
@@ -695,7 +721,7 @@ __global__ __launch_bounds__(64) void k_adj_grad_own(PassArrays a, Phys ph, cons
         lH += lpsi * Vi * dWH;
         for (int f = 0; f < 5; f++) lphi_i[f] -= t[f];
         for (int c = 0; c < 3; c++) lxi[c] -= ld[c];
-        if (j == jr && r > 0.0)
+        if (e == far.e && r > 0.0)
             for (int c = 0; c < 3; c++) {
                 // the farthest neighbour sets the limiter's length; its own term goes
                 // through the record (part two adds the same th for j)
@@ -703,20 +729,24 @@ __global__ __launch_bounds__(64) void k_adj_grad_own(PassArrays a, Phys ph, cons
                 lxi[c] -= th;
             }
     });
-    if (!act) return;
+    split_sum<SPLIT>(lV);
+    split_sum<SPLIT>(lH);
+    for (int f = 0; f < 5; f++) split_sum<SPLIT>(lphi_i[f]);
+    for (int c = 0; c < 3; c++) split_sum<SPLIT>(lxi[c]);
+    if (!act || sub != 0) return;
     int ix[16];
     double* lv = pa.lval + (long long)i * 12;
-    ix[0] = jr != i ? jr : -1;
+    ix[0] = far.e >= 0 ? holder(far) : -1;
     lv[L_HALF] = lhalf;
     for (int f = 0; f < 5; f++) {
         int tmax = -1, tmin = -1;
         if (lmax[f] != 0.0) {
-            if (jmax[f] == i) lphi_i[f] += lmax[f];
-            else tmax = jmax[f];
+            if (pmax[f].e < 0) lphi_i[f] += lmax[f];
+            else tmax = holder(pmax[f]);
         }
         if (lmin[f] != 0.0) {
-            if (jmin[f] == i) lphi_i[f] += lmin[f];
-            else tmin = jmin[f];
+            if (pmin[f].e < 0) lphi_i[f] += lmin[f];
+            else tmin = holder(pmin[f]);
         }
         ix[1 + f] = tmax;
         ix[6 + f] = tmin;
@@ -742,12 +772,14 @@ struct AdjPullLds {
     TeamLds<16> rec;
     TeamLds<4> lix;
 };
+template <int SPLIT>
 __global__ __launch_bounds__(64) void k_adj_grad_pull(PassArrays a, Phys ph, const int* __restrict__ counts,
                                                        const int* __restrict__ list, AdjArrays aj, PullArrays pa,
                                                        double* __restrict__ out_v, double* __restrict__ out_u) {
     __shared__ AdjPullLds S;
-    const int lane = threadIdx.x;
-    const int j_ = xcd_block_adj() * kWave + lane;
+    constexpr int kOwn = kWave / SPLIT;   // particles of the wave
+    const int lane = threadIdx.x, sub = lane / kOwn;
+    const int j_ = xcd_block_adj() * kOwn + lane % kOwn;
     const bool act = j_ < a.n;
     const int j = act ? j_ : a.n - 1;
     const long long n = a.n;
@@ -755,11 +787,15 @@ __global__ __launch_bounds__(64) void k_adj_grad_pull(PassArrays a, Phys ph, con
     const double rho_j = a.m[j] * a.nk[j];
     const double phi_j[5] = {rho_j, a.vx[j], a.vy[j], a.vz[j], (ph.gamma - 1.0) * rho_j * a.u[j]};
     double lphi[5], lx[3];
-    for (int f = 0; f < 5; f++) lphi[f] = pa.own[f * n + j];
-    for (int c = 0; c < 3; c++) lx[c] = pa.own[(5 + c) * n + j];
+    // (j's own side enters one lane's sums)
+    for (int f = 0; f < 5; f++) lphi[f] = sub == 0 ? pa.own[f * n + j] : 0.0;
+    for (int c = 0; c < 3; c++) lx[c] = sub == 0 ? pa.own[(5 + c) * n + j] : 0.0;
     const int cnum = act ? counts[j] : 0;
-    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i(cnum));
-    auto entry = [&](int k) { return k < cnum ? list[(long long)k * n + j] : -1; };
+    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i((cnum + SPLIT - 1) / SPLIT));
+    auto entry = [&](int k) {
+        const int e = k * SPLIT + sub;
+        return e < cnum ? list[(long long)e * n + j] : -1;
+    };
     auto start = [&](int i) {
         const int ir = i >= 0 ? i : j;
         team_load<8 * kAdjRec, 16>(S.rec, pa.rec, a.n, ir, lane);
@@ -813,7 +849,9 @@ __global__ __launch_bounds__(64) void k_adj_grad_pull(PassArrays a, Phys ph, con
             }
         }
     }
-    if (!act) return;
+    for (int f = 0; f < 5; f++) split_sum<SPLIT>(lphi[f]);
+    for (int c = 0; c < 3; c++) split_sum<SPLIT>(lx[c]);
+    if (!act || sub != 0) return;
     for (int c = 0; c < 3; c++) aj.acc_x[c * n + j] += lx[c];
     // j's adjoints of rho, v and P are complete: the outputs in v and u, and the
     // factor of j's radial terms in the kernel-length reverse
@@ -843,11 +881,13 @@ __global__ __launch_bounds__(64) void k_adj_grad_pull(PassArrays a, Phys ph, con
 // Each particle j walks its flux list, which holds its own gather set and every
 // i whose gather set holds j: the pair's radial terms are w'(r/H) times the
 // factor of whichever of the two has the other within its kernel length.
+template <int SPLIT>
 __global__ __launch_bounds__(64) void k_adj_length(PassArrays a, Phys ph, const int* __restrict__ counts,
                                                     const int* __restrict__ list, AdjArrays aj, PullArrays pa) {
     __shared__ TeamLds<4> S;
-    const int lane = threadIdx.x;
-    const int j_ = xcd_block_adj() * kWave + lane;
+    constexpr int kOwn = kWave / SPLIT;   // particles of the wave
+    const int lane = threadIdx.x, sub = lane / kOwn;
+    const int j_ = xcd_block_adj() * kOwn + lane % kOwn;
     const bool act = j_ < a.n;
     const int j = act ? j_ : a.n - 1;
     const long long n = a.n;
@@ -863,8 +903,11 @@ __global__ __launch_bounds__(64) void k_adj_length(PassArrays a, Phys ph, const 
     }
     double lx[3] = {0.0, 0.0, 0.0};
     const int cnum = act ? counts[j] : 0;
-    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i(cnum));
-    auto entry = [&](int k) { return k < cnum ? list[(long long)k * n + j] : -1; };
+    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i((cnum + SPLIT - 1) / SPLIT));
+    auto entry = [&](int k) {
+        const int e = k * SPLIT + sub;
+        return e < cnum ? list[(long long)e * n + j] : -1;
+    };
     int i = entry(0), inext = entry(1);
     if (kmax > 0) team_load<8 * kLenRec, 3>(S, pa.len, a.n, i >= 0 ? i : j, lane);
     for (int k = 0; k < kmax; k++) {
@@ -888,10 +931,33 @@ __global__ __launch_bounds__(64) void k_adj_length(PassArrays a, Phys ph, const 
         const double s = ((qi < 1.0 ? rc[4] * spline_dw(qi) : 0.0) + (qj < 1.0 ? fj * spline_dw(qj) : 0.0)) / r;
         for (int c = 0; c < 3; c++) lx[c] += s * d[c];
     }
-    if (!act) return;
+    for (int c = 0; c < 3; c++) split_sum<SPLIT>(lx[c]);
+    if (!act || sub != 0) return;
     for (int c = 0; c < 3; c++) aj.acc_x[c * n + j] += lx[c];
 }
 
+template <int SPLIT>
+static void launch_lists(const PassArrays& a, const Phys& ph, const int* counts, const int* gcount, const int* list,
+                         const AdjRecords& ar, const AdjArrays& aj, const PullArrays& pa, double* out_v, double* out_u,
+                         hipStream_t s) {
+    const int blocks = (a.n + kWave / SPLIT - 1) / (kWave / SPLIT);
+    k_adj_pairs<SPLIT><<<blocks, kWave, 0, s>>>(a, ph, counts, list, ar, aj);
+    // (two lanes cost the gather loops 201 us for 177 at 262,144: their lists are
+    // alike, and the limiter's part is run by both)
+    constexpr int kGather = SPLIT == 8 ? 8 : 1;
+    k_adj_grad_own<kGather><<<(a.n + kWave / kGather - 1) / (kWave / kGather), kWave, 0, s>>>(a, ph, gcount, list, ar,
+                                                                                             aj, pa);
+    k_adj_grad_pull<SPLIT><<<blocks, kWave, 0, s>>>(a, ph, counts, list, aj, pa, out_v, out_u);
+    k_adj_length<SPLIT><<<blocks, kWave, 0, s>>>(a, ph, counts, list, aj, pa);
+}
+
+// A particle's list is shared by eight lanes up to kAdjSplit8 particles (too few
+// waves for the chip otherwise), by two beyond (a wave waits for the longest of
+// 32 lists, not of 64).  Whole pass reverse, one / two / four / eight lanes:
+// lattice 4,096 255 / 142 / 87 / 64 us, 32,768 - / 166 / 161 / 174, 110,592 445 /
+// 429 / 427 / 495, 262,144 913 / 885 / 961 / 1,122; clustered 32,768 908 / 480 /
+// 328 / 266, 262,144 1,977 / 1,542 / 1,379 / 1,419.
+constexpr int kAdjSplit8 = 32768;
 void launch_pass_adjoint(const PassArrays& a, const Phys& ph, const int* counts, const int* gcount,
                          const int* list, const double* lam_dp, const double* lam_dE, double* scratch,
                          double* out_x, double* out_v, double* out_u, hipStream_t s) {
@@ -915,10 +981,10 @@ void launch_pass_adjoint(const PassArrays& a, const Phys& ph, const int* counts,
     pa.len = ar.ngb;   // the gather loops are done with the neighbour records by then
     const int blocks = (int)((n + kWave - 1) / kWave);
     k_adj_side_pack<<<blocks, kWave, 0, s>>>(a, ph, lam_dp, lam_dE, ar);
-    k_adj_pairs<<<blocks, kWave, 0, s>>>(a, ph, counts, list, ar, aj);
-    k_adj_grad_own<<<blocks, kWave, 0, s>>>(a, ph, gcount, list, ar, aj, pa);
-    k_adj_grad_pull<<<blocks, kWave, 0, s>>>(a, ph, counts, list, aj, pa, out_v, out_u);
-    k_adj_length<<<blocks, kWave, 0, s>>>(a, ph, counts, list, aj, pa);
+    if (a.n <= kAdjSplit8)
+        launch_lists<8>(a, ph, counts, gcount, list, ar, aj, pa, out_v, out_u, s);
+    else
+        launch_lists<2>(a, ph, counts, gcount, list, ar, aj, pa, out_v, out_u, s);
 }
 
 // ------------------------------------------------------------ step reverse
