@@ -451,6 +451,14 @@ __device__ __forceinline__ unsigned long long deposit_bits(unsigned v, unsigned 
     return r;
 }
 
+// the low ten bits of v, two zero bits between neighbours
+__device__ __forceinline__ unsigned dilate3(unsigned v) {
+    v = (v | (v << 16)) & 0x030000ffu;
+    v = (v | (v << 8)) & 0x0300f00fu;
+    v = (v | (v << 4)) & 0x030c30c3u;
+    return (v | (v << 2)) & 0x09249249u;
+}
+
 // Sum of two deposited values modulo 2^popcount(mask): with the bits outside the
 // mask set to one, carries run through them to the next mask bit.
 __device__ __forceinline__ unsigned long long dilated_add(unsigned long long x, unsigned long long y,
@@ -649,6 +657,9 @@ __device__ __forceinline__ void scan_cells(const TreeDesc& td, const int2* __res
     // slack for the rounding of cell edges, of the keys' quantisation and of the distances in FP32
     const double Rg = Rq * (1.0 + 1e-9) + 1e-12 * fmax(td.box[0], fmax(td.box[1], td.box[2])), iRg = 1.0 / Rg;
     const float Rg2 = 1.000001f;
+    // Sides of one length up to ten levels deep have every third bit each: the bits
+    // are spread in 12 instructions an axis (deposit_bits takes 11 for each bit)
+    const bool even = L <= 10 && td.qbits[0] == td.qbits[1] && td.qbits[0] == td.qbits[2];
     wave_lds_sync();
 #pragma unroll
     for (int d = 0; d < 3; d++) {
@@ -657,7 +668,9 @@ __device__ __forceinline__ void scan_cells(const TreeDesc& td, const int2* __res
         const unsigned long long image = u < 0 ? 0 : u >= nc ? 2 : 1;
         const double s = td.cs[L][d], clo = u * s;
         const double g = (wrap >> d) & 1 ? 0.0 : fmax(0.0, fmax(clo - bmax[d], bmin[d] - (clo + s)));
-        S.key[d][lane] = deposit_bits((unsigned)u & (nc - 1), td.mask[L][d]) | (image << (kImageBit + 2 * d));
+        const unsigned v = (unsigned)u & (nc - 1);
+        const unsigned long long bits = even ? dilate3(v) << (2 - d) : deposit_bits(v, td.mask[L][d]);
+        S.key[d][lane] = bits | (image << (kImageBit + 2 * d));
         const float q = (float)(g * iRg);
         S.dist2[d][lane] = q * q * 0.9999998f;
     }
