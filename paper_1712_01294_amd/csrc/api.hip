@@ -357,10 +357,12 @@ static mfm_status build(mfm_ctx* c, mfm_particles* p, hipStream_t s, double* con
     // each batch: one launch copies its arrays to the staging, one gathers them back in key order
     GatherBatch gb, cb;
     gb.count = cb.count = 0;
+    double4* pos = c->pos;   // packed with the first batch, which begins with x, y, z
     auto flush = [&]() {
         launch_copy_batch(n, cb, s);
-        launch_gather(n, gb, c->idx, s);
+        launch_gather(n, gb, c->idx, pos, s);
         gb.count = cb.count = 0;
+        pos = nullptr;
     };
     auto add = [&](void* ptr) {
         if (!ptr) return;
@@ -394,7 +396,6 @@ static mfm_status build(mfm_ctx* c, mfm_particles* p, hipStream_t s, double* con
     for (int k = 0; k < nextra; k++) add(extra[k]);
     flush();
     launch_tables(n, c->keys, c->td, c->tab, s);
-    launch_pos4(n, p->x, p->y, p->z, c->pos, s);
     c->n_tree = n;
     c->have_h = c->have_grad = c->have_flux = 0;
     c->last = s;

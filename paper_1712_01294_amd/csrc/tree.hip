@@ -185,8 +185,120 @@ void exclusive_scan(int m, const int* in, int* out, int* tmp, hipStream_t s) {
     }
 }
 
+// The same sort for up to 16 x 1024 keys of at most 32 bits, by one block in one
+// launch: the keys sit in registers, R per thread in the order (wave, round,
+// lane), and are exchanged through LDS once per digit.  The launches of the tiled
+// sort (three per digit and two copies) took 40 us for 4,096 keys of 18 bits,
+// nearly all of it their start and end; this takes one of
+// 15 us; 8,000 keys 49 -> 19 us, 10,648 54 -> 30 us.
+constexpr int kSmallWaves = 16;
+template <int R, int WIDTH>
+__global__ __launch_bounds__(kSmallWaves * kWave) void k_sort_small(int n, int bits, unsigned long long* __restrict__ keys,
+                                                                     int* __restrict__ vals) {
+    constexpr int kThreads = kSmallWaves * kWave;
+    __shared__ unsigned skey[R * kThreads];
+    __shared__ unsigned short sfrom[R * kThreads];
+    __shared__ int count[kSmallWaves][257];   // per wave and digit, then their first places (odd rows: few bank conflicts)
+    __shared__ int total[kSmallWaves];
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int e0 = wave * R * kWave + lane;   // element of round r: e0 + r kWave
+    unsigned key[R], from[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int e = e0 + r * kWave;
+        key[r] = e < n ? (unsigned)keys[e] : 0u;
+        from[r] = (unsigned)e;
+    }
+    const int d4 = threadIdx.x / 4, w4 = threadIdx.x % 4 * 4;   // the digit and the four waves whose counts the thread sums
+    constexpr unsigned mask = (1u << WIDTH) - 1u;
+    for (int shift = 0; shift < bits; shift += WIDTH) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) count[w4 + q][d4] = 0;
+        __syncthreads();
+        int at[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const bool valid = e0 + r * kWave < n;
+            const unsigned d = (key[r] >> shift) & mask;
+            // the lanes with the same digit: those that agree on each of its bits
+            const unsigned long long v = __ballot(valid);
+            unsigned lo = (unsigned)v, hi = (unsigned)(v >> 32);
+#pragma unroll
+            for (int b = 0; b < WIDTH; b++) {
+                const unsigned bit = 0u - ((d >> b) & 1u);
+                const unsigned long long m = __ballot((d & (1u << b)) != 0u);
+                lo &= ~((unsigned)m ^ bit);
+                hi &= ~((unsigned)(m >> 32) ^ bit);
+            }
+            int* const c = &count[wave][d];
+            const int before = *c;
+            const int rank = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+            wave_lds_sync();
+            if (valid && rank == 0) *c = before + __popc(lo) + __popc(hi);
+            wave_lds_sync();
+            at[r] = before + rank;
+        }
+        __syncthreads();
+        int c[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) c[q] = count[w4 + q][d4];
+        const int sum = c[0] + c[1] + c[2] + c[3], upto = wave_prefix_sum(sum);
+        if (lane == kWave - 1) total[wave] = upto;
+        __syncthreads();
+        int first = upto - sum;
+        for (int w = 0; w < wave; w++) first += total[w];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            count[w4 + q][d4] = first;
+            first += c[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; r++)
+            if (e0 + r * kWave < n) {
+                const int p = count[wave][(key[r] >> shift) & mask] + at[r];
+                skey[p] = key[r];
+                sfrom[p] = (unsigned short)from[r];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; r++)
+            if (e0 + r * kWave < n) {
+                key[r] = skey[e0 + r * kWave];
+                from[r] = sfrom[e0 + r * kWave];
+            }
+    }
+    int val[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) val[r] = e0 + r * kWave < n ? vals[from[r]] : 0;
+    wait_vmem();   // every value is here before the first is overwritten
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; r++)
+        if (e0 + r * kWave < n) {
+            keys[e0 + r * kWave] = key[r];
+            vals[e0 + r * kWave] = val[r];
+        }
+}
+
+template <int WIDTH>
+static void sort_small(int n, int bits, unsigned long long* keys, int* vals, hipStream_t s) {
+    constexpr int kThreads = kSmallWaves * kWave;
+    if (n <= 4 * kThreads) k_sort_small<4, WIDTH><<<1, kThreads, 0, s>>>(n, bits, keys, vals);
+    else if (n <= 8 * kThreads) k_sort_small<8, WIDTH><<<1, kThreads, 0, s>>>(n, bits, keys, vals);
+    else k_sort_small<16, WIDTH><<<1, kThreads, 0, s>>>(n, bits, keys, vals);
+}
+
 void radix_sort(int n, int bits, unsigned long long* keys, int* vals, unsigned long long* ktmp,
                 int* vtmp, int* hist, int* scan_tmp, hipStream_t s) {
+    constexpr int kThreads = kSmallWaves * kWave;
+    if (n <= 16 * kThreads && bits <= 32) {
+        const int passes = (bits + 7) / 8;
+        if (bits <= 6 * passes) sort_small<6>(n, bits, keys, vals, s);
+        else if (bits <= 7 * passes) sort_small<7>(n, bits, keys, vals, s);
+        else sort_small<8>(n, bits, keys, vals, s);
+        return;
+    }
     int nblocks = (n + kTile - 1) / kTile;
     unsigned long long *ka = keys, *kb = ktmp;
     int *va = vals, *vb = vtmp;
@@ -210,12 +322,24 @@ void radix_sort(int n, int bits, unsigned long long* keys, int* vals, unsigned l
 }
 
 // --------------------------------------------------- reorder in place
-__global__ void k_gather_batch(int n, GatherBatch gb, const int* __restrict__ idx) {
+// (with pos, the first three arrays, the positions, also go there packed for the
+// neighbour scans: one 32-byte load per particle)
+__global__ void k_gather_batch(int n, GatherBatch gb, const int* __restrict__ idx, double4* __restrict__ pos) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     int src = idx[i];
     if (src < 0 || src >= n) return;   // only reachable if the sort were wrong
-    for (int a = 0; a < gb.count; a++) gb.dst[a][i] = gb.src[a][src];
+    int a = 0;
+    if (pos) {
+        double x[3];
+        for (; a < 3; a++) {
+            const unsigned long long v = gb.src[a][src];
+            gb.dst[a][i] = v;
+            x[a] = __longlong_as_double((long long)v);
+        }
+        pos[i] = make_double4(x[0], x[1], x[2], 0.0);
+    }
+    for (; a < gb.count; a++) gb.dst[a][i] = gb.src[a][src];
 }
 
 __global__ void k_fill_u64(long long m, unsigned long long* __restrict__ p, unsigned long long v) {
@@ -286,8 +410,8 @@ void launch_keys(int n, const double* x, const double* y, const double* z, const
     k_keys<<<(n + 255) / 256, 256, 0, s>>>(n, x, y, z, td, keys, idx);
 }
 
-void launch_gather(int n, const GatherBatch& gb, const int* idx, hipStream_t s) {
-    k_gather_batch<<<(n + 255) / 256, 256, 0, s>>>(n, gb, idx);
+void launch_gather(int n, const GatherBatch& gb, const int* idx, double4* pos, hipStream_t s) {
+    k_gather_batch<<<(n + 255) / 256, 256, 0, s>>>(n, gb, idx, pos);
 }
 
 void launch_reset_counters(Counters* c, hipStream_t s) {
