@@ -354,24 +354,19 @@ static mfm_status build(mfm_ctx* c, mfm_particles* p, hipStream_t s, double* con
     c->tab_keys_n = -1;
     launch_keys(n, p->x, p->y, p->z, c->td, c->keys, c->idx, s);
     radix_sort(n, c->td.ktot, c->keys, c->idx, c->ktmp, c->vtmp, c->hist, c->scan_tmp, s);
-    // each batch: one launch copies its arrays to the staging, one gathers them back in key order
-    GatherBatch gb, cb;
-    gb.count = cb.count = 0;
+    // in batches: one launch lays the arrays out as records, one reads them back in key order
+    GatherBatch gb;
+    gb.count = 0;
     double4* pos = c->pos;   // packed with the first batch, which begins with x, y, z
     auto flush = [&]() {
-        launch_copy_batch(n, cb, s);
-        launch_gather(n, gb, c->idx, pos, s);
-        gb.count = cb.count = 0;
+        launch_reorder(n, gb, c->gtmp, c->idx, pos, s);
+        gb.count = 0;
         pos = nullptr;
     };
     auto add = [&](void* ptr) {
         if (!ptr) return;
-        if (gb.count == kGatherMax) flush();   // staging full: reorder this batch, then reuse the staging
-        unsigned long long* stage = c->gtmp + (long long)gb.count * n;
-        cb.src[cb.count] = (const unsigned long long*)ptr;
-        cb.dst[cb.count] = stage;
-        cb.count++;
-        gb.src[gb.count] = stage;
+        if (gb.count == kReorderMax) flush();   // staging full: reorder this batch, then reuse the staging
+        gb.src[gb.count] = (const unsigned long long*)ptr;
         gb.dst[gb.count] = (unsigned long long*)ptr;
         gb.count++;
     };

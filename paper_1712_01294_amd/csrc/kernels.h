@@ -34,8 +34,11 @@ void radix_sort(int n, int bits, unsigned long long* keys, int* vals, unsigned l
                 int* vtmp, int* hist, int* scan_tmp, hipStream_t s);
 void launch_keys(int n, const double* x, const double* y, const double* z, const TreeDesc& td,
                  unsigned long long* keys, int* idx, hipStream_t s);
-// (pos: null, or the packed positions of a batch whose first arrays are x, y, z)
-void launch_gather(int n, const GatherBatch& gb, const int* idx, double4* pos, hipStream_t s);
+// up to kReorderMax arrays of the batch (in place: dst[a] may be src[a]) by idx
+// through n 128-byte records; pos: null, or the packed positions of a batch whose
+// first arrays are x, y, z
+constexpr int kReorderMax = 16;
+void launch_reorder(int n, const GatherBatch& gb, unsigned long long* rec, const int* idx, double4* pos, hipStream_t s);
 void launch_fill_u64(long long m, unsigned long long* p, unsigned long long v, hipStream_t s);
 // all counter copies to their start values in one launch
 void launch_reset_counters(Counters* c, hipStream_t s);

@@ -322,24 +322,61 @@ void radix_sort(int n, int bits, unsigned long long* keys, int* vals, unsigned l
 }
 
 // --------------------------------------------------- reorder in place
+// Up to 16 arrays at a time: they are laid out as one 128-byte record per
+// particle, and each particle of the new order then reads its record whole.
+// Gathered from copies of the arrays, 8 bytes of each, particles given in no
+// order took a 64-byte line of memory per particle and array.  The records leave
+// and arrive through LDS, so that memory sees whole lines both ways.  Measured
+// (both kernels, 12 arrays): 16.8M particles in random order 4.3 -> 1.6 ms; 2.1M
+// nearly in order 0.22 ms as before.
+static_assert(kReorderMax == 16, "a record is one 128-byte line");
+constexpr int kRecordArrays = kReorderMax;
+__global__ __launch_bounds__(256) void k_records_out(int n, GatherBatch gb, unsigned long long* __restrict__ rec) {
+    __shared__ TeamLds<8> lds[256 / kWave];
+    TeamLds<8>& S = lds[threadIdx.x / kWave];
+    const int lane = threadIdx.x % kWave;
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    const bool act = i < n;
+    const unsigned long long lanes = __ballot(act);
+    unsigned long long v[kRecordArrays];
+#pragma unroll
+    for (int a = 0; a < kRecordArrays; a++) v[a] = act && a < gb.count ? gb.src[a][i] : 0ull;
+#pragma unroll
+    for (int c = 0; c < kRecordArrays / 2; c++) {
+        uint4 u;
+        __builtin_memcpy(&u, v + 2 * c, 16);
+        team_put(S, c, lane, u);
+    }
+    wave_lds_sync();
+    team_store<8 * kRecordArrays>(S, rec + (size_t)(unsigned)(i - lane) * kRecordArrays, lanes, lane);
+}
+
 // (with pos, the first three arrays, the positions, also go there packed for the
 // neighbour scans: one 32-byte load per particle)
-__global__ void k_gather_batch(int n, GatherBatch gb, const int* __restrict__ idx, double4* __restrict__ pos) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    int src = idx[i];
-    if (src < 0 || src >= n) return;   // only reachable if the sort were wrong
-    int a = 0;
-    if (pos) {
-        double x[3];
-        for (; a < 3; a++) {
-            const unsigned long long v = gb.src[a][src];
-            gb.dst[a][i] = v;
-            x[a] = __longlong_as_double((long long)v);
-        }
-        pos[i] = make_double4(x[0], x[1], x[2], 0.0);
+__global__ __launch_bounds__(256) void k_records_in(int n, GatherBatch gb, const unsigned long long* __restrict__ rec,
+                                                    const int* __restrict__ idx, double4* __restrict__ pos) {
+    __shared__ TeamLds<8> lds[256 / kWave];
+    TeamLds<8>& S = lds[threadIdx.x / kWave];
+    const int lane = threadIdx.x % kWave;
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int src = i < n ? idx[i] : -1;
+    const bool act = src >= 0 && src < n;   // (in [0, n) unless the sort were wrong)
+    team_load<8 * kRecordArrays, kRecordArrays / 2>(S, rec, n, act ? src : 0, lane);
+    wait_vmem();
+    wave_lds_sync();
+    unsigned long long v[kRecordArrays];
+#pragma unroll
+    for (int c = 0; c < kRecordArrays / 2; c++) {
+        const uint4 u = team_chunk(S, c, lane);
+        __builtin_memcpy(v + 2 * c, &u, 16);
     }
-    for (; a < gb.count; a++) gb.dst[a][i] = gb.src[a][src];
+    if (!act) return;
+#pragma unroll
+    for (int a = 0; a < kRecordArrays; a++)
+        if (a < gb.count) gb.dst[a][i] = v[a];
+    if (pos)
+        pos[i] = make_double4(__longlong_as_double((long long)v[0]), __longlong_as_double((long long)v[1]),
+                              __longlong_as_double((long long)v[2]), 0.0);
 }
 
 __global__ void k_fill_u64(long long m, unsigned long long* __restrict__ p, unsigned long long v) {
@@ -410,8 +447,10 @@ void launch_keys(int n, const double* x, const double* y, const double* z, const
     k_keys<<<(n + 255) / 256, 256, 0, s>>>(n, x, y, z, td, keys, idx);
 }
 
-void launch_gather(int n, const GatherBatch& gb, const int* idx, double4* pos, hipStream_t s) {
-    k_gather_batch<<<(n + 255) / 256, 256, 0, s>>>(n, gb, idx, pos);
+void launch_reorder(int n, const GatherBatch& gb, unsigned long long* rec, const int* idx, double4* pos, hipStream_t s) {
+    if (n <= 0 || gb.count <= 0) return;
+    k_records_out<<<(n + 255) / 256, 256, 0, s>>>(n, gb, rec);
+    k_records_in<<<(n + 255) / 256, 256, 0, s>>>(n, gb, rec, idx, pos);
 }
 
 void launch_reset_counters(Counters* c, hipStream_t s) {
