@@ -73,8 +73,8 @@ def binding(frac_hbm, frac_alu):
     return "alu" if frac_alu >= frac_hbm else "hbm"
 
 
-KERNEL_NAMES = {"solve_h": "k_solve_h<false> + k_solve_h_wave + k_solve_h_fallback",
-                "gradients": "k_gradients<false, false>", "hydro_fluxes": "k_fluxes_f64"}
+KERNEL_NAMES = {"solve_h": "k_solve_h<false> + k_root_h<false> + k_solve_h_wave + k_solve_h_fallback",
+                "gradients": "k_gradients", "hydro_fluxes": "k_fluxes_f64"}
 KERNEL_SOURCES = ("paper_1712_01294_amd/csrc/pass.hip", "paper_1712_01294_amd/csrc/device.h",
                   "paper_1712_01294_amd/csrc/kernels.h")
 
@@ -83,14 +83,14 @@ KERNEL_SOURCES = ("paper_1712_01294_amd/csrc/pass.hip", "paper_1712_01294_amd/cs
 # known size (bench.py --copy-probe).  Keyed by workload and kernel, and valid
 # only for the kernel sources whose fingerprint is recorded with it.
 TRAFFIC = {
-    ("clustered", "solve_h"): {"bytes_per_launch": 1.2331e+11, "fingerprint": "4d9f0a385d8119e7"},
-    ("clustered", "gradients"): {"bytes_per_launch": 3.0494e+10, "fingerprint": "4d9f0a385d8119e7"},
-    ("clustered", "hydro_fluxes"): {"bytes_per_launch": 1.3791e+10, "fingerprint": "4d9f0a385d8119e7"},
-    ("clustered", "solve_h_mixed"): {"bytes_per_launch": 1.2331e+11, "fingerprint": "4d9f0a385d8119e7"},
-    ("clustered", "gradients_mixed"): {"bytes_per_launch": 2.7638e+10, "fingerprint": "4d9f0a385d8119e7"},
-    ("clustered", "hydro_fluxes_mixed"): {"bytes_per_launch": 1.5502e+10, "fingerprint": "4d9f0a385d8119e7"},
-    ("clustered", "hydro_fluxes_mfv"): {"bytes_per_launch": 1.4172e+10, "fingerprint": "4d9f0a385d8119e7"},
-    ("clustered", "hydro_fluxes_mfv_mixed"): {"bytes_per_launch": 1.5410e+10, "fingerprint": "4d9f0a385d8119e7"},
+    ("clustered", "solve_h"): {"bytes_per_launch": 6.9962e+10, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "gradients"): {"bytes_per_launch": 1.9230e+10, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "hydro_fluxes"): {"bytes_per_launch": 1.1004e+10, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "solve_h_mixed"): {"bytes_per_launch": 6.9962e+10, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "gradients_mixed"): {"bytes_per_launch": 1.6564e+10, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "hydro_fluxes_mixed"): {"bytes_per_launch": 1.3685e+10, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "hydro_fluxes_mfv"): {"bytes_per_launch": 1.1187e+10, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "hydro_fluxes_mfv_mixed"): {"bytes_per_launch": 1.4436e+10, "fingerprint": "62625c00f6c9d468"},
 }
 
 # VALU counters per launch from rocprofv3 --pmc passes over this benchmark:
@@ -98,14 +98,14 @@ TRAFFIC = {
 # percentage (SQ_ACTIVE_INST_VALU over GRBM_GUI_ACTIVE, 256 CUs) and VALU
 # instructions issued.  Keyed and fingerprinted like TRAFFIC.
 COUNTERS = {
-    ("clustered", "solve_h"): {"valu_busy_pct": 70.6, "fp64_flops_per_launch": 7.3894e+11, "fp32_flops_per_launch": 6.2724e+09, "valu_insts_per_launch": 1.7271e+10, "fingerprint": "4d9f0a385d8119e7"},
-    ("clustered", "gradients"): {"valu_busy_pct": 27.7, "fp64_flops_per_launch": 1.0868e+11, "fp32_flops_per_launch": 0.0000e+00, "valu_insts_per_launch": 2.1952e+09, "fingerprint": "4d9f0a385d8119e7"},
-    ("clustered", "hydro_fluxes"): {"valu_busy_pct": 52.4, "fp64_flops_per_launch": 3.6667e+11, "fp32_flops_per_launch": 0.0000e+00, "valu_insts_per_launch": 5.7054e+09, "fingerprint": "4d9f0a385d8119e7"},
-    ("clustered", "solve_h_mixed"): {"valu_busy_pct": 70.6, "fp64_flops_per_launch": 7.3894e+11, "fp32_flops_per_launch": 6.2724e+09, "valu_insts_per_launch": 1.7271e+10, "fingerprint": "4d9f0a385d8119e7"},
-    ("clustered", "gradients_mixed"): {"valu_busy_pct": 30.1, "fp64_flops_per_launch": 9.3961e+10, "fp32_flops_per_launch": 1.4820e+10, "valu_insts_per_launch": 2.2503e+09, "fingerprint": "4d9f0a385d8119e7"},
-    ("clustered", "hydro_fluxes_mixed"): {"valu_busy_pct": 77.4, "fp64_flops_per_launch": 6.8311e+10, "fp32_flops_per_launch": 2.7785e+11, "valu_insts_per_launch": 5.8521e+09, "fingerprint": "4d9f0a385d8119e7"},
-    ("clustered", "hydro_fluxes_mfv"): {"valu_busy_pct": 61.8, "fp64_flops_per_launch": 4.8855e+11, "fp32_flops_per_launch": 0.0000e+00, "valu_insts_per_launch": 7.2402e+09, "fingerprint": "4d9f0a385d8119e7"},
-    ("clustered", "hydro_fluxes_mfv_mixed"): {"valu_busy_pct": 95.6, "fp64_flops_per_launch": 7.0260e+10, "fp32_flops_per_launch": 3.9681e+11, "valu_insts_per_launch": 7.3923e+09, "fingerprint": "4d9f0a385d8119e7"},
+    ("clustered", "solve_h"): {"valu_busy_pct": 67.6, "fp64_flops_per_launch": 3.7692e+11, "fp32_flops_per_launch": 1.3868e+10, "valu_insts_per_launch": 1.1158e+10, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "gradients"): {"valu_busy_pct": 49.8, "fp64_flops_per_launch": 1.0313e+11, "fp32_flops_per_launch": 0.0000e+00, "valu_insts_per_launch": 2.5951e+09, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "hydro_fluxes"): {"valu_busy_pct": 70.2, "fp64_flops_per_launch": 3.0003e+11, "fp32_flops_per_launch": 0.0000e+00, "valu_insts_per_launch": 4.8677e+09, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "solve_h_mixed"): {"valu_busy_pct": 67.6, "fp64_flops_per_launch": 3.7692e+11, "fp32_flops_per_launch": 1.3868e+10, "valu_insts_per_launch": 1.1158e+10, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "gradients_mixed"): {"valu_busy_pct": 55.0, "fp64_flops_per_launch": 8.8414e+10, "fp32_flops_per_launch": 1.4820e+10, "valu_insts_per_launch": 2.6355e+09, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "hydro_fluxes_mixed"): {"valu_busy_pct": 105.6, "fp64_flops_per_launch": 6.0808e+10, "fp32_flops_per_launch": 2.5345e+11, "valu_insts_per_launch": 5.5647e+09, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "hydro_fluxes_mfv"): {"valu_busy_pct": 77.6, "fp64_flops_per_launch": 4.1126e+11, "fp32_flops_per_launch": 0.0000e+00, "valu_insts_per_launch": 6.2626e+09, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "hydro_fluxes_mfv_mixed"): {"valu_busy_pct": 115.6, "fp64_flops_per_launch": 6.2620e+10, "fp32_flops_per_launch": 3.6198e+11, "valu_insts_per_launch": 6.9639e+09, "fingerprint": "62625c00f6c9d468"},
 }
 
 

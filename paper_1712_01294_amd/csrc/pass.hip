@@ -1104,16 +1104,16 @@ __global__ void k_pack_prim_active(PassArrays a, Phys ph, const int* __restrict_
     for (int k = 0; k < cnum; k++) pack_one(a, ph, prim, list[(long long)k * n + i]);
 }
 
-// One wave per block; the neighbours' records come by lane teams, and while one is summed the next is on its way to LDS.  The tail
-// appends of the wave queue in LDS until the sums are done: in the loop a wave
-// had an atomic's round trip to L2 in nearly every step.  Then the queue is
-// worked off 64 at a time, four rounds in flight; the entries of a round that go
-// to one bin take their places with one atomic.  The flux records leave through
-// LDS too, in whole 128-byte lines: 16-byte stores 256 bytes apart reached memory
-// as partial lines.  Three waves per SIMD: the sums, the record in hand and the
-// loop's values take 140 VGPRs, and a fourth wave spills.  Measured: lattice
-// 2.1M 1.06 -> 0.81 ms, clustered 16.8M 13.8 -> 9.2 ms, shock tube 295k (mixed)
-// 0.177 -> 0.114 ms.
+// One wave per block; the neighbours' records come by lane teams, and while one is
+// summed the next is on its way to LDS.  The tail appends of the wave queue in LDS
+// until the sums are done: in the loop a wave had an atomic's round trip to L2 in
+// nearly every step.  Then the queue is worked off 64 at a time, four rounds in
+// flight; the entries of a round that go to one bin take their places with one
+// atomic.  The flux records leave through LDS too, in whole 128-byte lines: 16-byte
+// stores 256 bytes apart reached memory as partial lines.  Three waves per SIMD: the
+// sums, the record in hand and the loop's values take 140 VGPRs, and a fourth wave
+// spills.  Measured: lattice 2.1M 1.06 -> 0.81 ms, clustered 16.8M 13.8 -> 9.2 ms,
+// shock tube 295k (mixed) 0.177 -> 0.114 ms.
 // With HIER (hierarchical steps with active subsets) only the particles of
 // mode kModeSolve get new gradients; a kept particle with a gather list only
 // appends itself to the lists of its active neighbours that do not reach it.
