@@ -616,8 +616,10 @@ __device__ __forceinline__ int row_candidate(int r) { return 16 * ((r >> 2) & 1)
 // periodic axis d whole; displacements along such an axis must then take the
 // minimum image themselves.  bmin, bmax and Rq must be uniform over the wave,
 // with Rq below half of every periodic side.
-template <typename Chunk>
-__device__ __forceinline__ void scan_cells(const TreeDesc& td, const int2* __restrict__ tab,
+// With WHOLE false a scan that would span an axis whole is not made: the result
+// says whether it was.
+template <bool WHOLE = true, typename Chunk>
+__device__ __forceinline__ bool scan_cells(const TreeDesc& td, const int2* __restrict__ tab,
                                            const double4* __restrict__ pos, ScanLds& S, int lane,
                                            const double bmin[3], const double bmax[3], double Rq, Chunk&& chunk,
                                            double scale = kScanScale) {
@@ -652,7 +654,8 @@ __device__ __forceinline__ void scan_cells(const TreeDesc& td, const int2* __res
         if (!wide || L == 0) break;
     }
     wrap = __builtin_amdgcn_readfirstlane(wrap);
-    if (cnt[0] <= 0 || cnt[1] <= 0 || cnt[2] <= 0) return;
+    if (!WHOLE && wrap) return false;
+    if (cnt[0] <= 0 || cnt[1] <= 0 || cnt[2] <= 0) return true;
     const int ncells = cnt[0] * cnt[1] * cnt[2];
     // slack for the rounding of cell edges, of the keys' quantisation and of the distances in FP32
     const double Rg = Rq * (1.0 + 1e-9) + 1e-12 * fmax(td.box[0], fmax(td.box[1], td.box[2])), iRg = 1.0 / Rg;
@@ -719,6 +722,7 @@ __device__ __forceinline__ void scan_cells(const TreeDesc& td, const int2* __res
             wave_lds_sync();   // the next chunk overwrites the owners
         }
     }
+    return true;
 }
 
 // The lanes one group scan serves: of the lanes that still need one, those with
@@ -766,8 +770,9 @@ __device__ __forceinline__ ScanClass scan_class(bool need, double R, const doubl
 // waits for the busiest one once per stage, not once per 64 candidates.
 // Measured with both (solve stage): clustered 16.8M particles 44.6 -> 36.8 ms,
 // jittered lattice 2.1M 1.79 -> 1.41 ms.
-template <typename Hit>
-__device__ __forceinline__ void group_scan(const TreeDesc& td, const int2* __restrict__ tab,
+// (WHOLE as in scan_cells)
+template <bool WHOLE, typename Hit>
+__device__ __forceinline__ bool group_scan(const TreeDesc& td, const int2* __restrict__ tab,
                                            const double4* __restrict__ pos, GroupLds& S, int lane,
                                            const double bmin[3], const double bmax[3], double Rq, double pad,
                                            const double xi[3], double R2, bool sel, Hit&& hit) {
@@ -792,7 +797,7 @@ __device__ __forceinline__ void group_scan(const TreeDesc& td, const int2* __res
         for (int g = 0; g < kStage; g += kWave) {
             unsigned long long m = 0;
             if (g < ns) {
-                if (spans) {
+                if (WHOLE && spans) {
                     m = wrap_mask(S, g, xi, R2, spans, td.box);
                 } else {
                     float f[3] = {(float)((S.x[g + row] - cen[0]) * scale), (float)((S.y[g + row] - cen[1]) * scale),
@@ -829,13 +834,13 @@ __device__ __forceinline__ void group_scan(const TreeDesc& td, const int2* __res
             cur &= 0x7fffffffu >> b;
             left--;
             const int k = base + b;
-            const double r2 = sq_disp(make_double4(S.x[k], S.y[k], S.z[k], 0.0), xi, spans, td.box);
+            const double r2 = sq_disp(make_double4(S.x[k], S.y[k], S.z[k], 0.0), xi, WHOLE ? spans : 0, td.box);
             if (r2 < R2) hit(S.j[k], r2);
         }
         wave_lds_sync();   // the next candidates overwrite the stage
         ns = 0;
     };
-    scan_cells(td, tab, pos, S.cells, lane, bmin, bmax, Rq + pad, [&](const double4& q, bool valid, int nb, int wrap) {
+    const bool made = scan_cells<WHOLE>(td, tab, pos, S.cells, lane, bmin, bmax, Rq + pad, [&](const double4& q, bool valid, int nb, int wrap) {
         spans = wrap;
         if (ns + nb > kStage) drain();
         if (valid) {
@@ -847,6 +852,7 @@ __device__ __forceinline__ void group_scan(const TreeDesc& td, const int2* __res
         ns += nb;
     });
     if (ns > 0) drain();
+    return made;
 }
 
 }  // namespace mfm

@@ -259,11 +259,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
     double* __restrict__ rp = rl + i;
     int* __restrict__ jp = jl + i;
     bool need = act && R > 0.0;
+    // A group whose scan spans a periodic axis whole (a thin box) is left to the list
+    // solver, whose single spheres rarely do: its tests would need the minimum image
+    // of every pair, off the matrix cores.  Measured (solve stage, shock tubes of
+    // 14, 18 and 24 spacings across): 549 -> 238, 653 -> 200, 840 -> 273 us.
+    bool unmade = false;
     for (int pass = 0; pass < kWave; pass++) {
         if (__ballot(need) == 0) break;
         const ScanClass cl = scan_class(need, R, xi);
         const double iR = 1.0 / R, iT0 = 1.0 / Ht0, iT1 = 1.0 / Ht1;
-        group_scan(td, tab, pos, S, lane, cl.bmin, cl.bmax, cl.Rq, HIER ? *pad : 0.0, xi, R * R, cl.in, [&](int j, double r2) {
+        const bool made = group_scan<false>(td, tab, pos, S, lane, cl.bmin, cl.bmax, cl.Rq, HIER ? *pad : 0.0, xi, R * R, cl.in, [&](int j, double r2) {
             const double r = sqrt_mid(r2);
             if (m < cap) {
                 *rp = r;
@@ -276,6 +281,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
             st0 += spline_w(r * iT0);
             st1 += spline_w(r * iT1);
         });
+        unmade = unmade || (cl.in && !made);
         need = need && !cl.in;
     }
     // A bracket with every radius below it listed is narrowed by the trial counts
@@ -311,8 +317,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kSolveWaves
         // hand over to the per-particle solver: the bracket and the next trial
         // radius, in the particle's own (now unused) radius slots 0-2
         double Rn = R;
-        if (!(R > 0.0)) {
-            // no scan without a radius (positions that are not numbers)
+        if (!(R > 0.0) || unmade) {
+            // no scan without a radius (positions that are not numbers), or none made
             hi = INFINITY;
         } else if (!(neff >= ph.n_ngb)) {
             // grow by the density estimate, at least 1.15x, at most 4x
@@ -846,7 +852,7 @@ __global__ __launch_bounds__(256) void k_gather_kept(PassArrays a, TreeDesc td, 
     bool need = sel && Rs > 0.0;
     for (int pass = 0; pass < kWave && __ballot(need); pass++) {
         const ScanClass cl = scan_class(need, Rs, xi);
-        group_scan(td, tab, pos, S, lane, cl.bmin, cl.bmax, cl.Rq, *pad, xi, Rs * Rs, cl.in, [&](int j, double r2) {
+        group_scan<true>(td, tab, pos, S, lane, cl.bmin, cl.bmax, cl.Rq, *pad, xi, Rs * Rs, cl.in, [&](int j, double r2) {
             const double r = sqrt_mid(r2);
             if (r < H && j != i) {
                 if (c < cap) jl[(long long)c * n + i] = j;
