@@ -83,14 +83,14 @@ KERNEL_SOURCES = ("paper_1712_01294_amd/csrc/pass.hip", "paper_1712_01294_amd/cs
 # known size (bench.py --copy-probe).  Keyed by workload and kernel, and valid
 # only for the kernel sources whose fingerprint is recorded with it.
 TRAFFIC = {
-    ("clustered", "solve_h"): {"bytes_per_launch": 6.9962e+10, "fingerprint": "62625c00f6c9d468"},
-    ("clustered", "gradients"): {"bytes_per_launch": 1.9230e+10, "fingerprint": "62625c00f6c9d468"},
-    ("clustered", "hydro_fluxes"): {"bytes_per_launch": 1.1004e+10, "fingerprint": "62625c00f6c9d468"},
-    ("clustered", "solve_h_mixed"): {"bytes_per_launch": 6.9962e+10, "fingerprint": "62625c00f6c9d468"},
-    ("clustered", "gradients_mixed"): {"bytes_per_launch": 1.6564e+10, "fingerprint": "62625c00f6c9d468"},
-    ("clustered", "hydro_fluxes_mixed"): {"bytes_per_launch": 1.3685e+10, "fingerprint": "62625c00f6c9d468"},
-    ("clustered", "hydro_fluxes_mfv"): {"bytes_per_launch": 1.1187e+10, "fingerprint": "62625c00f6c9d468"},
-    ("clustered", "hydro_fluxes_mfv_mixed"): {"bytes_per_launch": 1.4436e+10, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "solve_h"): {"bytes_per_launch": 6.9823e+10, "fingerprint": "7bfc954fb1d7a067"},
+    ("clustered", "gradients"): {"bytes_per_launch": 1.9207e+10, "fingerprint": "7bfc954fb1d7a067"},
+    ("clustered", "hydro_fluxes"): {"bytes_per_launch": 1.1008e+10, "fingerprint": "7bfc954fb1d7a067"},
+    ("clustered", "solve_h_mixed"): {"bytes_per_launch": 6.9823e+10, "fingerprint": "7bfc954fb1d7a067"},
+    ("clustered", "gradients_mixed"): {"bytes_per_launch": 1.6566e+10, "fingerprint": "7bfc954fb1d7a067"},
+    ("clustered", "hydro_fluxes_mixed"): {"bytes_per_launch": 1.3725e+10, "fingerprint": "7bfc954fb1d7a067"},
+    ("clustered", "hydro_fluxes_mfv"): {"bytes_per_launch": 1.1187e+10, "fingerprint": "7bfc954fb1d7a067"},
+    ("clustered", "hydro_fluxes_mfv_mixed"): {"bytes_per_launch": 1.4450e+10, "fingerprint": "7bfc954fb1d7a067"},
 }
 
 # VALU counters per launch from rocprofv3 --pmc passes over this benchmark:
@@ -98,14 +98,14 @@ TRAFFIC = {
 # percentage (SQ_ACTIVE_INST_VALU over GRBM_GUI_ACTIVE, 256 CUs) and VALU
 # instructions issued.  Keyed and fingerprinted like TRAFFIC.
 COUNTERS = {
-    ("clustered", "solve_h"): {"valu_busy_pct": 67.6, "fp64_flops_per_launch": 3.7692e+11, "fp32_flops_per_launch": 1.3868e+10, "valu_insts_per_launch": 1.1158e+10, "fingerprint": "62625c00f6c9d468"},
-    ("clustered", "gradients"): {"valu_busy_pct": 49.8, "fp64_flops_per_launch": 1.0313e+11, "fp32_flops_per_launch": 0.0000e+00, "valu_insts_per_launch": 2.5951e+09, "fingerprint": "62625c00f6c9d468"},
-    ("clustered", "hydro_fluxes"): {"valu_busy_pct": 70.2, "fp64_flops_per_launch": 3.0003e+11, "fp32_flops_per_launch": 0.0000e+00, "valu_insts_per_launch": 4.8677e+09, "fingerprint": "62625c00f6c9d468"},
-    ("clustered", "solve_h_mixed"): {"valu_busy_pct": 67.6, "fp64_flops_per_launch": 3.7692e+11, "fp32_flops_per_launch": 1.3868e+10, "valu_insts_per_launch": 1.1158e+10, "fingerprint": "62625c00f6c9d468"},
-    ("clustered", "gradients_mixed"): {"valu_busy_pct": 55.0, "fp64_flops_per_launch": 8.8414e+10, "fp32_flops_per_launch": 1.4820e+10, "valu_insts_per_launch": 2.6355e+09, "fingerprint": "62625c00f6c9d468"},
-    ("clustered", "hydro_fluxes_mixed"): {"valu_busy_pct": 105.6, "fp64_flops_per_launch": 6.0808e+10, "fp32_flops_per_launch": 2.5345e+11, "valu_insts_per_launch": 5.5647e+09, "fingerprint": "62625c00f6c9d468"},
-    ("clustered", "hydro_fluxes_mfv"): {"valu_busy_pct": 77.6, "fp64_flops_per_launch": 4.1126e+11, "fp32_flops_per_launch": 0.0000e+00, "valu_insts_per_launch": 6.2626e+09, "fingerprint": "62625c00f6c9d468"},
-    ("clustered", "hydro_fluxes_mfv_mixed"): {"valu_busy_pct": 115.6, "fp64_flops_per_launch": 6.2620e+10, "fp32_flops_per_launch": 3.6198e+11, "valu_insts_per_launch": 6.9639e+09, "fingerprint": "62625c00f6c9d468"},
+    ("clustered", "solve_h"): {"valu_busy_pct": 67.6, "fp64_flops_per_launch": 3.7682e+11, "fp32_flops_per_launch": 1.3868e+10, "valu_insts_per_launch": 1.1109e+10, "fingerprint": "7bfc954fb1d7a067"},
+    ("clustered", "gradients"): {"valu_busy_pct": 50.1, "fp64_flops_per_launch": 1.0313e+11, "fp32_flops_per_launch": 0.0000e+00, "valu_insts_per_launch": 2.5951e+09, "fingerprint": "7bfc954fb1d7a067"},
+    ("clustered", "hydro_fluxes"): {"valu_busy_pct": 70.5, "fp64_flops_per_launch": 3.0003e+11, "fp32_flops_per_launch": 0.0000e+00, "valu_insts_per_launch": 4.8677e+09, "fingerprint": "7bfc954fb1d7a067"},
+    ("clustered", "solve_h_mixed"): {"valu_busy_pct": 67.6, "fp64_flops_per_launch": 3.7682e+11, "fp32_flops_per_launch": 1.3868e+10, "valu_insts_per_launch": 1.1109e+10, "fingerprint": "7bfc954fb1d7a067"},
+    ("clustered", "gradients_mixed"): {"valu_busy_pct": 54.2, "fp64_flops_per_launch": 8.8414e+10, "fp32_flops_per_launch": 1.4820e+10, "valu_insts_per_launch": 2.6355e+09, "fingerprint": "7bfc954fb1d7a067"},
+    ("clustered", "hydro_fluxes_mixed"): {"valu_busy_pct": 105.9, "fp64_flops_per_launch": 6.0808e+10, "fp32_flops_per_launch": 2.5345e+11, "valu_insts_per_launch": 5.5647e+09, "fingerprint": "7bfc954fb1d7a067"},
+    ("clustered", "hydro_fluxes_mfv"): {"valu_busy_pct": 77.8, "fp64_flops_per_launch": 4.1126e+11, "fp32_flops_per_launch": 0.0000e+00, "valu_insts_per_launch": 6.2626e+09, "fingerprint": "7bfc954fb1d7a067"},
+    ("clustered", "hydro_fluxes_mfv_mixed"): {"valu_busy_pct": 116.4, "fp64_flops_per_launch": 6.2620e+10, "fp32_flops_per_launch": 3.6198e+11, "valu_insts_per_launch": 6.9639e+09, "fingerprint": "7bfc954fb1d7a067"},
 }
 
 
